@@ -1217,6 +1217,11 @@ static hipError_t numeric_impl(const Problem *dpr, const BinPlan &bp, const WsLa
                       sizeof(VT) == 8, st);
       continue;
     }
+    if (sort_rows_ok(b, bp.n)) {
+      launch_num_sort(dpr, rows, hdr, b, bins_count(bp, b, b), crp, ccol, cval, sizeof(VT) == 8,
+                      fb, st);
+      continue;
+    }
     if (G < 8) G = 8;
     if (G == kWave && num_wave_lds_bytes(b, sizeof(VT), pack) <= D.lds_per_block) {
       launch_num_wave(dpr, rows, hdr, b, sub_log2(bp, b, G), bins_count(bp, b, b),
