@@ -3,17 +3,26 @@
 // light preprocessing step before the product; with prow = pcol it is the
 // symmetric permutation P A P^T).
 //
-// Steps: the inverse row permutation (each new row reads its old row), with
-// a check that both arrays are permutations; the new row lengths, their scan
-// into B's row pointer, and lists of the new rows by length class; then
-// every new row gathers its old row, maps the columns and writes them in
-// ascending order.  The new columns of a row are distinct, so an element's
+// Steps: the inverse permutations by plain stores, and a check that both
+// arrays are permutations: every index in range and found again at its own
+// place; the new row lengths, their scan into B's row pointer, and lists of
+// the old rows by length class; then every old row, in its own order (A is
+// read as a stream, and the rows of a band map the same columns one after
+// the other), maps its columns and writes them in ascending order at the new
+// row's place.  The new columns of a row are distinct, so an element's
 // output slot is the number of the row's elements with a smaller new
-// column: short rows count it over the row's columns staged in LDS (group of
-// G lanes, up to 4 elements per lane; one kernel per length class, each over
-// its own list), rows longer than 4096 entries go through column panels (a
-// bitmap of the panel's columns, a block scan of its words, then each
-// element writes at its rank).
+// column: rows of at most 4096 entries count it over the row's columns
+// staged in LDS, longer rows go through column panels (a bitmap of the
+// panel's columns, a block scan of its words, then each element writes at
+// its rank).
+//
+// Bound by chains of dependent reads and by the scattered rows of the result.
+// 2^20 rows of 16 on diagonal bands, FP32 (0.50 -> 0.22 ms in all): the check
+// 23 us instead of 90 (compare-and-swap into a cleared inverse, twice also
+// for equal arrays), lengths and lists 23 instead of 191 (one atomic per wave
+// and class on one cache line), the rows 141 instead of 197 (203 new row by
+// new row, which reads A's rows at random; 172 one row at a time per group;
+// 155 with eight blocks a CU instead of four).
 #include <algorithm>
 
 #include "internal.hpp"
@@ -21,155 +30,268 @@
 
 namespace spg {
 
-constexpr int kPermE = 4;          // elements per lane in the short-row kernels
 constexpr int kPermLong = 4096;    // rows longer than this take the panel kernel
 constexpr int kPermPanelBits = 32768;  // columns per panel (one bitmap word per thread)
 
-__global__ __launch_bounds__(256) void k_perm_clear(int32_t *a, int64_t n) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x)
-    a[i] = -1;
+// inv[p[i]] = i for the indices in range (a repeated one: any of them).
+__global__ __launch_bounds__(256) void k_perm_inverse(const int32_t *__restrict__ p, int m,
+                                                      int32_t *__restrict__ pinv,
+                                                      const int32_t *__restrict__ q, int n,
+                                                      int32_t *__restrict__ qinv) {
+  const int64_t t0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t step = (int64_t)gridDim.x * blockDim.x;
+  if (p)
+    for (int64_t i = t0; i < m; i += step) {
+      const int v = p[i];
+      if ((unsigned)v < (unsigned)m) pinv[v] = (int)i;
+    }
+  if (q)
+    for (int64_t i = t0; i < n; i += step) {
+      const int v = q[i];
+      if ((unsigned)v < (unsigned)n) qinv[v] = (int)i;
+    }
 }
 
-// inv[p[i]] = i; a value out of range or taken twice raises kStatInvalid.
-__global__ __launch_bounds__(256) void k_perm_inverse(const int32_t *__restrict__ p, int n,
-                                                      int32_t *__restrict__ inv, WsHeader *hdr) {
+// p is a permutation exactly when all its indices are in range and each is
+// the last (only) one stored at its place.
+__global__ __launch_bounds__(256) void k_perm_check(const int32_t *__restrict__ p, int m,
+                                                    const int32_t *__restrict__ pinv,
+                                                    const int32_t *__restrict__ q, int n,
+                                                    const int32_t *__restrict__ qinv,
+                                                    WsHeader *hdr) {
+  const int64_t t0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t step = (int64_t)gridDim.x * blockDim.x;
   bool bad = false;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    const int v = p[i];
-    if (v < 0 || v >= n) bad = true;
-    else if (atomicCAS(&inv[v], -1, (int)i) != -1) bad = true;
-  }
+  if (p)
+    for (int64_t i = t0; i < m; i += step) {
+      const int v = p[i];
+      bad = bad || (unsigned)v >= (unsigned)m || pinv[v] != (int)i;
+    }
+  if (q)
+    for (int64_t i = t0; i < n; i += step) {
+      const int v = q[i];
+      bad = bad || (unsigned)v >= (unsigned)n || qinv[v] != (int)i;
+    }
   if (bad) atomicOr(&hdr->status, kStatInvalid);
 }
 
-// Length classes of the new rows: (0, 64], (64, 256], (256, 1024],
-// (1024, 4096] (group kernels of 16, 64, 256, 1024 lanes) and longer (the
+// Length classes of the new rows: (0, 16], (16, 64], (64, 256] (groups of
+// 16, 16 and 64 lanes), (256, 4096] (one block per row) and longer (the
 // panel kernel); empty rows need no work.
 constexpr int kPermClasses = 5;
 
 __device__ __forceinline__ int perm_class(int len) {
-  return len <= 0 ? -1 : len <= 64 ? 0 : len <= 256 ? 1 : len <= 1024 ? 2 : len <= kPermLong ? 3 : 4;
+  return len <= 0 ? -1 : len <= 16 ? 0 : len <= 64 ? 1 : len <= 256 ? 2 : len <= kPermLong ? 3 : 4;
 }
 
-// Length of every new row, and the row in its class's list (class c's list
-// holds at most m rows at lists + c * m; its length is hdr->bin_count[c]).
-// Each wave takes one atomic per class for its rows.
+// Length of every new row, and the old row in its class's list (class c's
+// list holds at most m rows at lists + c * m; its length is
+// hdr->bin_count[c]).  A block takes a run of consecutive rows, so that one
+// atomic per class and block reserves its places; the rows of a list stay in
+// runs.
 __global__ __launch_bounds__(256) void k_perm_len(const int32_t *__restrict__ arp,
-                                                  const int32_t *__restrict__ rinv, int m,
-                                                  int32_t *__restrict__ cnt,
+                                                  const int32_t *__restrict__ prow, int m,
+                                                  int per, int32_t *__restrict__ cnt,
                                                   int32_t *__restrict__ lists, WsHeader *hdr) {
+  __shared__ int have[kPermClasses], next[kPermClasses];
   if (hdr->status) return;
+  if (threadIdx.x < kPermClasses) have[threadIdx.x] = 0;
+  __syncthreads();
   const uint64_t below = lanes_below();
+  const int64_t lo = (int64_t)blockIdx.x * per, hi = min((int64_t)m, lo + per);
   // whole waves step together, so the ballots below see every lane
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t r0 = (int64_t)blockIdx.x * blockDim.x; r0 < m; r0 += stride) {
-    const int64_t r = r0 + threadIdx.x;
+  for (int64_t i0 = lo; i0 < hi; i0 += 256) {
+    const int64_t i = i0 + threadIdx.x;
     int cls = -1;
-    if (r < m) {
-      const int old = rinv ? rinv[r] : (int)r;
-      const int len = arp[old + 1] - arp[old];
-      cnt[r] = len;
+    if (i < hi) {
+      const int len = arp[i + 1] - arp[i];
+      cnt[prow ? prow[i] : i] = len;
       cls = perm_class(len);
     }
 #pragma unroll
     for (int c = 0; c < kPermClasses; ++c) {
       const uint64_t mk = __ballot(cls == c);
+      if (mk && lane_id() == 0) atomicAdd(&have[c], __popcll(mk));
+    }
+  }
+  __syncthreads();
+  if (threadIdx.x < kPermClasses)
+    next[threadIdx.x] = have[threadIdx.x] ? atomicAdd(&hdr->bin_count[threadIdx.x], have[threadIdx.x]) : 0;
+  __syncthreads();
+  for (int64_t i0 = lo; i0 < hi; i0 += 256) {
+    const int64_t i = i0 + threadIdx.x;
+    const int cls = i < hi ? perm_class(arp[i + 1] - arp[i]) : -1;
+#pragma unroll
+    for (int c = 0; c < kPermClasses; ++c) {
+      const uint64_t mk = __ballot(cls == c);
       if (mk == 0) continue;
-      const int leader = __ffsll((unsigned long long)mk) - 1;
       int base = 0;
-      if (lane_id() == leader) base = atomicAdd(&hdr->bin_count[c], __popcll(mk));
-      base = __shfl(base, leader);
-      if (cls == c) lists[(int64_t)c * m + base + __popcll(mk & below)] = (int)r;
+      if (lane_id() == 0) base = atomicAdd(&next[c], __popcll(mk));
+      base = __shfl(base, 0);
+      if (cls == c) lists[(int64_t)c * m + base + __popcll(mk & below)] = (int)i;
     }
   }
 }
 
-// Rows of length class `cls` (at most 4G entries): G lanes per row, elements
-// e = l + t G.
-template <int G, typename VT>
-__global__ __launch_bounds__(G <= kWave ? 256 : G) void k_perm_rows(
+// Rows of a length class (at most E G entries): G lanes per row, elements
+// e = l + t G of U rows at a time, so that U rows' chains of dependent reads
+// run side by side; the heads of the next rows (old row, its bounds, the new
+// row's place) are read while the current ones are written.
+template <int G, int E, int U, typename VT>
+__device__ __forceinline__ void perm_rows(const int32_t *__restrict__ arp,
+                                          const int32_t *__restrict__ acol,
+                                          const VT *__restrict__ aval,
+                                          const int32_t *__restrict__ prow,
+                                          const int32_t *__restrict__ pcol,
+                                          const int32_t *__restrict__ list, int count,
+                                          const int32_t *__restrict__ brp,
+                                          int32_t *__restrict__ bcol, VT *__restrict__ bval,
+                                          int *key_s) {
+  constexpr int CAP = E * G;  // places of a row in key_s
+  constexpr bool BLOCK = G > kWave;
+  static_assert(CAP % 4 == 0, "columns are compared four at a time");
+  const int R = (int)blockDim.x / G;
+  const int l = threadIdx.x % G;
+  const int ngroups = gridDim.x * R;
+  int idx = blockIdx.x * R + threadIdx.x / G;  // group g takes list entries g U .. g U + U - 1
+  // groups of one wave (or block) step together
+  int lead = blockIdx.x * R + (BLOCK ? 0 : (int)(threadIdx.x / kWave) * (kWave / G));
+  int i1[U], r1[U], i2[U], s[U], len[U], o[U];
+  auto rows_at = [&](int g, int (&i)[U]) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) i[u] = (int64_t)g * U + u < count ? list[g * U + u] : -1;
+  };
+  auto new_of = [&](const int (&i)[U], int (&r)[U]) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) r[u] = i[u] < 0 ? -1 : (prow ? prow[i[u]] : i[u]);
+  };
+  auto bounds = [&](const int (&i)[U], const int (&r)[U], int (&s)[U], int (&len)[U], int (&o)[U]) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      s[u] = len[u] = o[u] = 0;
+      if (i[u] >= 0) {
+        s[u] = arp[i[u]];
+        len[u] = arp[i[u] + 1] - s[u];
+        o[u] = brp[r[u]];
+      }
+    }
+  };
+  rows_at(idx, i1);
+  new_of(i1, r1);
+  bounds(i1, r1, s, len, o);
+  rows_at(idx + ngroups, i1);
+  new_of(i1, r1);
+  rows_at(idx + 2 * ngroups, i2);
+  const int nlists = (int)(((int64_t)count + U - 1) / U);
+  for (; lead < nlists; lead += ngroups, idx += ngroups) {
+    int key[U][E], rank[U][E];
+    VT v[U][E];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int t = 0; t < E; ++t) {
+        const int e = l + t * G;
+        key[u][t] = -1;
+        v[u][t] = VT(0);
+        rank[u][t] = 0;
+        if (e < len[u]) {
+          key[u][t] = acol[s[u] + e];
+          if (aval) v[u][t] = aval[s[u] + e];
+        }
+      }
+    int s1[U], len1[U], o1[U], r2[U], i3[U];
+    bounds(i1, r1, s1, len1, o1);
+    new_of(i2, r2);
+    rows_at(idx + 3 * ngroups, i3);
+    if (pcol) {
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int t = 0; t < E; ++t)
+          if (key[u][t] >= 0) key[u][t] = pcol[key[u][t]];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int t = 0; t < E; ++t)
+        key_s[u * CAP + l + t * G] = key[u][t] < 0 ? INT32_MAX : key[u][t];
+    group_sync<BLOCK>();
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      for (int q = 0; q < len[u]; q += 4) {  // places past the row rank last
+        const int4 k4 = *reinterpret_cast<const int4 *>(key_s + u * CAP + q);
+#pragma unroll
+        for (int t = 0; t < E; ++t)
+          rank[u][t] += (k4.x < key[u][t]) + (k4.y < key[u][t]) + (k4.z < key[u][t]) +
+                        (k4.w < key[u][t]);
+      }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int t = 0; t < E; ++t) {
+        if (key[u][t] >= 0) {
+          bcol[o[u] + rank[u][t]] = key[u][t];
+          if (bval) bval[o[u] + rank[u][t]] = v[u][t];
+        }
+      }
+    group_sync<BLOCK>();
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      s[u] = s1[u];
+      len[u] = len1[u];
+      o[u] = o1[u];
+      i1[u] = i2[u];
+      r1[u] = r2[u];
+      i2[u] = i3[u];
+    }
+  }
+}
+
+template <typename VT>
+__global__ __launch_bounds__(256) void k_perm_short(
     const int32_t *__restrict__ arp, const int32_t *__restrict__ acol,
-    const VT *__restrict__ aval, const int32_t *__restrict__ rinv,
-    const int32_t *__restrict__ pcol, const int32_t *__restrict__ list, int cls,
+    const VT *__restrict__ aval, const int32_t *__restrict__ prow,
+    const int32_t *__restrict__ pcol, const int32_t *__restrict__ lists, int m,
     const int32_t *__restrict__ brp, int32_t *__restrict__ bcol, VT *__restrict__ bval,
     const WsHeader *hdr) {
-  constexpr int WG = G <= kWave ? 256 : G;
-  constexpr int R = WG / G;
-  constexpr int CAP = kPermE * G;
-  __shared__ int skey[R * CAP];
+  __shared__ __align__(16) int skey[1024];
   if (hdr->status) return;
-  const int count = hdr->bin_count[cls];
-  const int rslot = threadIdx.x / G, l = threadIdx.x % G;
-  int *key_s = skey + rslot * CAP;
-  const int ngroups = gridDim.x * R;
-  for (int r0 = blockIdx.x * R; r0 < count; r0 += ngroups) {
-    const int idx = r0 + rslot;
-    int len = 0, s = 0, r = 0;
-    if (idx < count) {
-      r = list[idx];
-      const int old = rinv ? rinv[r] : r;
-      s = arp[old];
-      len = arp[old + 1] - s;
-    }
-    const bool mine = idx < count && len <= CAP;
-    int key[kPermE];
-    VT v[kPermE];
-#pragma unroll
-    for (int t = 0; t < kPermE; ++t) {
-      const int e = l + t * G;
-      key[t] = -1;
-      v[t] = VT(0);
-      if (mine && e < len) {
-        const int c = acol[s + e];
-        key[t] = pcol ? pcol[c] : c;
-        if (aval) v[t] = aval[s + e];
-        key_s[e] = key[t];
-      }
-    }
-    if (G > kWave) __syncthreads();
-    else group_sync<false>();
-    if (mine) {
-      const int o = brp[r];
-#pragma unroll
-      for (int t = 0; t < kPermE; ++t) {
-        if (key[t] < 0) continue;
-        int rank = 0;
-        for (int u = 0; u < len; ++u) rank += key_s[u] < key[t] ? 1 : 0;
-        bcol[o + rank] = key[t];
-        if (bval) bval[o + rank] = v[t];
-      }
-    }
-    if (G > kWave) __syncthreads();
-    else group_sync<false>();
-  }
+  const int t = threadIdx.x;
+  perm_rows<16, 1, 4, VT>(arp, acol, aval, prow, pcol, lists, hdr->bin_count[0], brp, bcol, bval,
+                       skey + t / 16 * 64);
+  perm_rows<16, 4, 1, VT>(arp, acol, aval, prow, pcol, lists + m, hdr->bin_count[1], brp, bcol, bval,
+                       skey + t / 16 * 64);
+  perm_rows<64, 4, 1, VT>(arp, acol, aval, prow, pcol, lists + (size_t)2 * m, hdr->bin_count[2], brp,
+                       bcol, bval, skey + t / 64 * 256);
 }
 
-// Rows longer than kPermLong: one block per row, panels of kPermPanelBits
-// new columns; in each panel a bitmap marks the row's columns, a block scan
+// One block per row: the rows of 257..kPermLong entries, then the longer
+// ones in panels of kPermPanelBits new columns; in each panel a bitmap marks the row's columns, a block scan
 // of the bitmap words gives each word's starting rank, and every element
 // writes at that rank plus the marks below it in its word (columns are
 // distinct).
 template <typename VT>
 __global__ __launch_bounds__(1024) void k_perm_long(
     const int32_t *__restrict__ arp, const int32_t *__restrict__ acol,
-    const VT *__restrict__ aval, const int32_t *__restrict__ rinv,
-    const int32_t *__restrict__ pcol, int ncols, const int32_t *__restrict__ longrows,
-    int cls, const int32_t *__restrict__ brp, int32_t *__restrict__ bcol, VT *__restrict__ bval,
+    const VT *__restrict__ aval, const int32_t *__restrict__ prow,
+    const int32_t *__restrict__ pcol, int m, int ncols, const int32_t *__restrict__ lists,
+    const int32_t *__restrict__ brp, int32_t *__restrict__ bcol, VT *__restrict__ bval,
     const WsHeader *hdr) {
   static_assert(kPermPanelBits / 32 == 1024, "one bitmap word per thread");
   __shared__ uint32_t bm[kPermPanelBits / 32];
   __shared__ int wpre[kPermPanelBits / 32];
   __shared__ int wtot[1024 / kWave];
+  __shared__ __align__(16) int skey[kPermLong];
   if (hdr->status) return;
-  const int count = hdr->bin_count[cls];
+  perm_rows<1024, 4, 1, VT>(arp, acol, aval, prow, pcol, lists + (size_t)3 * m, hdr->bin_count[3],
+                         brp, bcol, bval, skey);
+  const int32_t *longrows = lists + (size_t)4 * m;
+  const int count = hdr->bin_count[4];
   const int tid = threadIdx.x;
   for (int li = blockIdx.x; li < count; li += gridDim.x) {
-    const int r = longrows[li];
-    const int old = rinv ? rinv[r] : r;
-    const int s = arp[old], len = arp[old + 1] - s;
-    int base = brp[r];
+    const int i = longrows[li];
+    const int s = arp[i], len = arp[i + 1] - s;
+    int base = brp[prow ? prow[i] : i];
     for (int plo = 0; plo < ncols; plo += kPermPanelBits) {
       bm[tid] = 0u;
       __syncthreads();
@@ -214,41 +336,19 @@ size_t perm_workspace_bytes(int64_t m, int64_t n, size_t *rinv_off, size_t *cinv
   return o;
 }
 
-template <int G, typename VT>
-static void perm_rows_launch(const int32_t *arp, const int32_t *acol, const void *aval,
-                             const int32_t *rinv, const int32_t *pcol, int m,
-                             const int32_t *lists, int cls, const int32_t *brp, int32_t *bcol,
-                             void *bval, const WsHeader *hdr, int cus, hipStream_t st) {
-  constexpr int WG = G <= kWave ? 256 : G;
-  constexpr int R = WG / G;
-  // a persistent grid over the class's list (its length is on the device)
-  const int need = (m + R - 1) / R;
-  const int grid = std::max(1, std::min(need, cus * (2048 / WG)));
-  hipLaunchKernelGGL((k_perm_rows<G, VT>), dim3(grid), dim3(WG), 0, st, arp, acol,
-                     static_cast<const VT *>(aval), rinv, pcol, lists + (size_t)cls * m, cls,
-                     brp, bcol, static_cast<VT *>(bval), hdr);
-}
-
 template <typename VT>
 static hipError_t permute_impl(const int32_t *arp, const int32_t *acol, const void *aval,
-                               const int32_t *rinv, const int32_t *pcol, int m, int n,
+                               const int32_t *prow, const int32_t *pcol, int m, int n,
                                const int32_t *brp, int32_t *bcol, void *bval,
-                               const int32_t *longrows, const WsHeader *hdr, hipStream_t st) {
+                               const int32_t *lists, const WsHeader *hdr, hipStream_t st) {
   const DevInfo &D = dev_info();
-  static_assert(kPermE * 16 == 64 && kPermE * 64 == 256 && kPermE * 256 == 1024 &&
-                    kPermE * 1024 == kPermLong,
-                "the length classes match the group sizes");
-  perm_rows_launch<16, VT>(arp, acol, aval, rinv, pcol, m, longrows, 0, brp, bcol, bval, hdr,
-                           D.cus, st);
-  perm_rows_launch<64, VT>(arp, acol, aval, rinv, pcol, m, longrows, 1, brp, bcol, bval, hdr,
-                           D.cus, st);
-  perm_rows_launch<256, VT>(arp, acol, aval, rinv, pcol, m, longrows, 2, brp, bcol, bval, hdr,
-                            D.cus, st);
-  perm_rows_launch<1024, VT>(arp, acol, aval, rinv, pcol, m, longrows, 3, brp, bcol, bval, hdr,
-                             D.cus, st);
-  hipLaunchKernelGGL((k_perm_long<VT>), dim3(D.cus), dim3(1024), 0, st, arp, acol,
-                     static_cast<const VT *>(aval), rinv, pcol, n,
-                     longrows + (size_t)4 * m, 4, brp, bcol,
+  // persistent grids over the classes' lists (their lengths are on the device)
+  const int grid = std::max(1, std::min((m + 15) / 16, D.cus * 4));
+  hipLaunchKernelGGL((k_perm_short<VT>), dim3(grid), dim3(256), 0, st, arp, acol,
+                     static_cast<const VT *>(aval), prow, pcol, lists, m, brp, bcol,
+                     static_cast<VT *>(bval), hdr);
+  hipLaunchKernelGGL((k_perm_long<VT>), dim3(std::max(1, std::min(m, D.cus))), dim3(1024), 0, st,
+                     arp, acol, static_cast<const VT *>(aval), prow, pcol, m, n, lists, brp, bcol,
                      static_cast<VT *>(bval), hdr);
   return hipGetLastError();
 }
@@ -265,24 +365,25 @@ hipError_t launch_permute(const spg_csr &A, const int32_t *prow, const int32_t *
   int32_t *longrows = reinterpret_cast<int32_t *>(ws + lo);
   const DevInfo &D = dev_info();
   const int g = D.cus * 4;
-  if (prow) {
-    hipLaunchKernelGGL(k_perm_clear, dim3(g), dim3(256), 0, st, rinv, (int64_t)m);
-    hipLaunchKernelGGL(k_perm_inverse, dim3(g), dim3(256), 0, st, prow, m, rinv, hdr);
+  // the column array is checked as well (its inverse is not used); equal
+  // arrays of equal length are checked once
+  const int32_t *q = pcol == prow && m == n ? nullptr : pcol;
+  if (prow || q) {
+    hipLaunchKernelGGL(k_perm_inverse, dim3(g), dim3(256), 0, st, prow, m, rinv, q, n, cinv);
+    hipLaunchKernelGGL(k_perm_check, dim3(g), dim3(256), 0, st, prow, m, rinv, q, n, cinv, hdr);
   }
-  if (pcol) {  // the inverse itself is not needed, only the check
-    hipLaunchKernelGGL(k_perm_clear, dim3(g), dim3(256), 0, st, cinv, (int64_t)n);
-    hipLaunchKernelGGL(k_perm_inverse, dim3(g), dim3(256), 0, st, pcol, n, cinv, hdr);
-  }
-  hipLaunchKernelGGL(k_perm_len, dim3(g), dim3(256), 0, st, A.row_ptr, rinv, m, brp, longrows,
-                     hdr);
+  // runs of whole waves, at most g blocks
+  const int per = (int)((((int64_t)m + g - 1) / g + 255) / 256 * 256);
+  hipLaunchKernelGGL(k_perm_len, dim3(std::max(1, (m + per - 1) / std::max(1, per))), dim3(256), 0,
+                     st, A.row_ptr, prow, m, per, brp, longrows, hdr);
   WsLayout L{};
   L.scanpart = so;
   hipError_t e = launch_scan(brp, m, -1, L, ws, st);
   if (e != hipSuccess) return e;
   if (dtype == SPG_F64)
-    return permute_impl<double>(A.row_ptr, A.col_idx, A.vals, rinv, pcol, m, n, brp, bcol, bval,
+    return permute_impl<double>(A.row_ptr, A.col_idx, A.vals, prow, pcol, m, n, brp, bcol, bval,
                                 longrows, hdr, st);
-  return permute_impl<float>(A.row_ptr, A.col_idx, A.vals, rinv, pcol, m, n, brp, bcol, bval,
+  return permute_impl<float>(A.row_ptr, A.col_idx, A.vals, prow, pcol, m, n, brp, bcol, bval,
                              longrows, hdr, st);
 }
 
