@@ -10,6 +10,12 @@ from paper_2603_21444_amd import synth
 pytestmark = pytest.mark.gpu
 
 
+@pytest.fixture(scope="module", autouse=True)
+def _torch_first():
+    import torch  # brings up the HIP runtime that the library shares
+    assert torch.cuda.is_available()
+
+
 def _dev(p):
     import torch
     return torch.from_numpy(np.ascontiguousarray(p, dtype=np.int32)).cuda()
