@@ -99,6 +99,8 @@ struct MclInsert {
   }
 };
 
+constexpr int32_t kMclPending = -1;  // row length of a row that k_mcl_few gave back
+
 // LDS rows.  Key words pack (col | (128 + counter) << 24), n <= 2^24.
 template <int G>
 __global__ __launch_bounds__(MGeom<G>::WG) void k_mcl_rows(
@@ -106,7 +108,7 @@ __global__ __launch_bounds__(MGeom<G>::WG) void k_mcl_rows(
     int bin, int lS, int TT, uint32_t mul, int maxwin, int r, int rpost, float prune, int topk,
     int cap,
     int32_t *__restrict__ ycol, float *__restrict__ yval, int32_t *__restrict__ ycnt,
-    int32_t *__restrict__ fb_rows) {
+    int32_t *__restrict__ fb_rows, const int32_t *__restrict__ failed) {
   using GM = MGeom<G>;
   constexpr bool BLOCK = GM::BLOCK;
   extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -128,8 +130,12 @@ __global__ __launch_bounds__(MGeom<G>::WG) void k_mcl_rows(
   const int start = hdr->bin_start[bin];
   const int c = TT / G;
   const int s0 = l * c;
-  for (int ri = blockIdx.x * GM::R + rslot; ri < count; ri += gridDim.x * GM::R) {
+  // after k_mcl_few: the rows it did not take, and those it gave back
+  const int taken = failed ? min(count, hdr->queue[bin]) : 0;
+  const int first = failed && failed[bin] == 0 ? taken : 0;
+  for (int ri = first + blockIdx.x * GM::R + rslot; ri < count; ri += gridDim.x * GM::R) {
     int i = rows[start + ri];
+    if (ri < taken && ycnt[i] != kMclPending) continue;
     if (G >= kWave) i = __builtin_amdgcn_readfirstlane(i);
     int4 *k4 = reinterpret_cast<int4 *>(key);
     for (int s = l; s < TT / 4; s += G) k4[s] = make_int4(kEmpty, kEmpty, kEmpty, kEmpty);
@@ -273,6 +279,269 @@ __global__ __launch_bounds__(MGeom<G>::WG) void k_mcl_rows(
     }
     if (l == 0) ycnt[i] = total < cap ? total : cap;
     group_sync<BLOCK>();
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Rows of many products on few columns (an iteration that has found its
+// clusters: the B rows of a cluster hold the same columns).  One block of 256
+// threads per row; at most kFewCols columns in an LDS hash with 64-bit
+// fixed-point accumulators (the scale as for the panel kernel below, so sums
+// do not depend on the order of the adds), products numbered over the row's
+// entries as in k_num_sort, so that every thread has four of them in flight.
+// A row with more columns is given back to k_mcl_rows (its length is set to
+// kMclPending); when a quarter of the rows taken so far were given back, the
+// rest of the bin is left to that kernel.
+//
+// k_mcl_rows sizes its table by the products, holds one row per CU, and its
+// float compare-and-swap adds collide.  2^16 rows in clusters of 64 (4356
+// products, 64 columns a row): 6.60 ms there, 1.10 here
+// (2000 vector instructions a wave and row issue 90 % of the time; one row
+// per atomic on the queue: 3.93 ms).
+constexpr int kFewNT = 256;
+constexpr int kFewSlots = 1024;
+constexpr int kFewCols = 512;
+constexpr int kFewWords = 256;  // marks of 8192 products at a time
+constexpr int kFewBin = 6;      // first bin tried: more than 256 products
+constexpr int kFewTry = 512;    // rows taken before the share given back counts
+constexpr int kFewTake = 8;     // rows per atomic on the queue (12 ns each on one word)
+
+struct FewEntry {
+  float a;
+  int b;  // first B position less the number of its first product
+};
+
+__global__ __launch_bounds__(kFewNT, 8) void k_mcl_few(
+    const Problem *__restrict__ pr, const int32_t *__restrict__ rows, WsHeader *__restrict__ hdr,
+    int bin, int r, int rpost, float prune, int topk, int cap, const double *__restrict__ rabs,
+    int32_t *__restrict__ ycol, float *__restrict__ yval, int32_t *__restrict__ ycnt,
+    int32_t *__restrict__ failed) {
+  __shared__ unsigned long long acc[kFewSlots];
+  __shared__ int key[kFewSlots];
+  __shared__ FewEntry ent[kFewNT];
+  __shared__ uint32_t mark[kFewWords];
+  __shared__ int wpre[kFewWords];
+  __shared__ int wtot[kFewNT / kWave];
+  __shared__ double redd[kFewNT / kWave];
+  __shared__ int redi[kFewNT / kWave];
+  __shared__ unsigned long long redu[kFewNT / kWave];
+  __shared__ __align__(16) int kcol[kFewCols + 4];
+  __shared__ int ncols, nlist, item;
+  if (hdr->status) return;
+  const int count = hdr->bin_count[bin];
+  const int start = hdr->bin_start[bin];
+  const int tid = threadIdx.x;
+  const Part &P = pr->part[0];
+  const SPG_GLOBAL int32_t *brp = gp(P.brp);
+  const SPG_GLOBAL int32_t *bcol = gp(P.bcol);
+  const SPG_GLOBAL float *bval = gp(static_cast<const float *>(P.bval));
+  constexpr int U = 4;
+  int it = 0, it1 = 0;  // rows taken from the queue, kFewTake at a time
+  while (true) {
+    __syncthreads();
+    if (tid == 0) {
+      if (it == it1) {
+        const int bad = __hip_atomic_load(&failed[bin], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        item = bad * 4 > max(kFewTry, it1) ? count : atomicAdd(&hdr->queue[bin], kFewTake);
+      }
+      ncols = 0;
+      nlist = 0;
+    }
+    for (int s = tid; s < kFewSlots; s += kFewNT) {
+      acc[s] = 0ull;
+      key[s] = kEmpty;
+    }
+    __syncthreads();
+    if (it == it1) {
+      it = item;
+      it1 = min(count, it + kFewTake);
+    }
+    if (it >= count) return;
+    const int i = rows[start + it++];
+    int as, ae;
+    a_row(P, i, as, ae);
+    // the scale: 2^(62 - ex) with the row's bound on sum |a b| below 2^ex
+    double sb = 0.0;
+    for (int e = as + tid; e < ae; e += kFewNT)
+      sb += fabs((double)gp(static_cast<const float *>(P.aval))[e]) * rabs[gp(P.acol)[e]];
+    const double bound = group_sum<true, kFewNT>(sb, redd) * (1.0 + 1.0 / 1048576.0);
+    double sigma = 1.0;
+    if (bound > 0.0 && bound < 1e300) {
+      int ex = 0;
+      (void)frexp(bound, &ex);
+      sigma = ldexp(1.0, 62 - (ex < -960 ? -960 : ex));
+    }
+    const double inv_sigma = 1.0 / sigma;  // exact: a power of two
+    // 1. expansion, chunks of kFewNT entries, 8192 products at a time
+    for (int c0 = as; c0 < ae && ncols <= kFewCols; c0 += kFewNT) {
+      int b0 = 0, len = 0;
+      float a = 0.f;
+      if (c0 + tid < ae) {
+        const int k = gp(P.acol)[c0 + tid];
+        a = gp(static_cast<const float *>(P.aval))[c0 + tid];
+        b0 = brp[k];
+        len = brp[k + 1] - b0;
+      }
+      int tot, live;
+      const int off = group_excl_scan<true, kFewNT>(len, tid, wtot, tot);
+      const int rank = group_excl_scan<true, kFewNT>(len > 0 ? 1 : 0, tid, wtot, live);
+      if (len > 0) ent[rank] = FewEntry{a, b0 - off};
+      for (int w0 = 0; w0 < tot; w0 += kFewWords * 32) {
+        // bit p - w0: product p is the last of its entry
+        mark[tid] = 0u;
+        __syncthreads();
+        const int last = off + len - 1 - w0;
+        if (len > 0 && last >= 0 && last < kFewWords * 32)
+          atomicOr(&mark[last >> 5], 1u << (last & 31));
+        const int before = __syncthreads_count(len > 0 && last < 0);  // entries done
+        int all;
+        wpre[tid] = before + group_excl_scan<true, kFewNT>(__popc(mark[tid]), tid, wtot, all);
+        __syncthreads();
+        const int hi = min(tot - w0, kFewWords * 32);
+        for (int p0 = tid; p0 < hi; p0 += U * kFewNT) {
+          int col[U];
+          float v[U];
+          FewEntry en[U];
+          bool in[U];
+#pragma unroll
+          for (int u = 0; u < U; ++u) {
+            const int p = p0 + u * kFewNT;
+            in[u] = p < hi;
+            const int pc = in[u] ? p : 0;
+            en[u] = ent[wpre[pc >> 5] + __popc(mark[pc >> 5] & ((1u << (pc & 31)) - 1u))];
+            en[u].b += w0 + pc;
+          }
+#pragma unroll
+          for (int u = 0; u < U; ++u) {
+            col[u] = bcol[en[u].b];
+            v[u] = bval[en[u].b];
+          }
+#pragma unroll
+          for (int u = 0; u < U; ++u) {
+            if (!in[u]) continue;
+            uint32_t h = scramble_slot((uint32_t)col[u], 10);
+            // at most one walk round the table (it can fill up before every
+            // thread sees that the row is given back)
+            for (int probes = 0; probes < kFewSlots; ++probes) {
+              int k = key[h];
+              if (k == kEmpty) {
+                k = atomicCAS(&key[h], kEmpty, col[u]);
+                if (k == kEmpty) atomicAdd(&ncols, 1);
+              }
+              if (k == kEmpty || k == col[u]) break;
+              h = (h + 1) & (kFewSlots - 1);
+            }
+            const long long q = __double2ll_rn((double)(en[u].a * v[u]) * sigma);
+            atomicAdd(&acc[h], (unsigned long long)q);
+          }
+          if (ncols > kFewCols) break;
+        }
+        __syncthreads();
+      }
+    }
+    __syncthreads();
+    if (ncols > kFewCols) {
+      if (tid == 0) {
+        ycnt[i] = kMclPending;
+        atomicAdd(&failed[bin], 1);
+      }
+      continue;
+    }
+    // 2.-4. inflation, row sum, prune (thread t: slots t + 256 j)
+    constexpr int J = kFewSlots / kFewNT;
+    int sc[J];
+    float sv[J];
+    double part = 0.0;
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+      const int s = tid + j * kFewNT;
+      sc[j] = key[s];
+      sv[j] = ipow((float)((double)(long long)acc[s] * inv_sigma), r);
+      part += sc[j] != kEmpty ? (double)sv[j] : 0.0;
+    }
+    const float S = (float)group_sum<true, kFewNT>(part, redd);
+    unsigned long long best = 0;
+    int kept = 0;
+    bool keep[J];
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+      const unsigned long long kk = vc_key(sv[j] / S, sc[j]);
+      sv[j] = sv[j] / S;
+      keep[j] = sc[j] != kEmpty && !(sv[j] < prune);
+      if (sc[j] != kEmpty && kk > best) best = kk;
+      kept += keep[j] ? 1 : 0;
+    }
+    const int nkept = group_sum<true, kFewNT>(kept, redi);
+    if (nkept > topk) {
+      // 5. the largest bit pattern tau with at least topk kept values >= tau;
+      //    ties at tau: the smallest columns
+      uint32_t lo = 0, hi = 0x7f800000u;
+      while (lo < hi) {
+        const uint32_t mid = lo + (hi - lo + 1) / 2;
+        int cc = 0;
+#pragma unroll
+        for (int j = 0; j < J; ++j) cc += keep[j] && __float_as_uint(sv[j]) >= mid ? 1 : 0;
+        if (group_sum<true, kFewNT>(cc, redi) >= topk) lo = mid;
+        else hi = mid - 1;
+      }
+      int gt = 0;
+#pragma unroll
+      for (int j = 0; j < J; ++j) gt += keep[j] && __float_as_uint(sv[j]) > lo ? 1 : 0;
+      const int need = topk - group_sum<true, kFewNT>(gt, redi);
+      // columns at tau, listed
+#pragma unroll
+      for (int j = 0; j < J; ++j)
+        if (keep[j] && __float_as_uint(sv[j]) == lo) kcol[atomicAdd(&nlist, 1)] = sc[j];
+      __syncthreads();
+      const int nt = nlist;
+#pragma unroll
+      for (int j = 0; j < J; ++j) {
+        if (!keep[j]) continue;
+        const uint32_t b = __float_as_uint(sv[j]);
+        int before = 0;
+        if (b == lo)
+          for (int t = 0; t < nt; ++t) before += kcol[t] < sc[j] ? 1 : 0;
+        keep[j] = b > lo || (b == lo && before < need);
+      }
+      __syncthreads();
+      if (tid == 0) nlist = 0;
+      __syncthreads();
+    }
+    if (nkept == 0) {  // 6. never empty: the largest entry
+      const unsigned long long bb = group_max_u64<true, kFewNT>(best, redu);
+      const int bcolm = (int)~(uint32_t)(bb & 0xffffffffu);
+#pragma unroll
+      for (int j = 0; j < J; ++j) keep[j] = sc[j] != kEmpty && sc[j] == bcolm;
+    }
+    // 7. the kept columns' new sum and order: rank = kept columns below
+    double part2 = 0.0;
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+      if (keep[j]) {
+        kcol[atomicAdd(&nlist, 1)] = sc[j];
+        part2 += (double)sv[j];
+      }
+    }
+    const float S2 = (float)group_sum<true, kFewNT>(part2, redd);
+    const int total = nlist;
+    if (tid < 4) kcol[total + tid] = INT32_MAX;
+    __syncthreads();
+    SPG_GLOBAL int32_t *cb = gpw(ycol) + (size_t)i * cap;
+    SPG_GLOBAL float *vb = gpw(yval) + (size_t)i * cap;
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+      if (!keep[j]) continue;
+      int rk = 0;
+      for (int t = 0; t < total; t += 4) {
+        const int4 c4 = *reinterpret_cast<const int4 *>(kcol + t);
+        rk += (c4.x < sc[j]) + (c4.y < sc[j]) + (c4.z < sc[j]) + (c4.w < sc[j]);
+      }
+      if (rk < cap) {
+        cb[rk] = sc[j];
+        vb[rk] = rpost == 0 ? sv[j] / S2 : ipow(sv[j], rpost);
+      }
+    }
+    if (tid == 0) ycnt[i] = total < cap ? total : cap;
   }
 }
 
@@ -675,11 +944,14 @@ __global__ __launch_bounds__(kPT) void k_mcl_panel(
   }
 }
 
-// Row sums of |x| in FP64 (the heavy kernel's fixed-point scale bound).
+// Row sums of |x| in FP64 (the bound behind the fixed-point scales); clears
+// the counts of rows given back by k_mcl_few.
 __global__ __launch_bounds__(256) void k_row_abs(const Problem *__restrict__ pr,
                                                  const WsHeader *__restrict__ hdr,
-                                                 double *__restrict__ rabs) {
+                                                 double *__restrict__ rabs,
+                                                 int32_t *__restrict__ failed) {
   if (hdr->status) return;
+  if (blockIdx.x == 0 && threadIdx.x < kNB) failed[threadIdx.x] = 0;
   const Part &P = pr->part[0];
   const int n = P.kdim;
   const int lane = lane_id();
@@ -722,10 +994,10 @@ template <int G>
 static void mcl_launch(const Problem *dpr, const int32_t *rows, WsHeader *hdr, int bin, int lS,
                        int TT, uint32_t mul, int maxwin, int r, int rpost, float prune, int topk,
                        int cap,
-                       int32_t *ycol, float *yval, int32_t *ycnt, int32_t *fb, int grid,
-                       size_t lds, hipStream_t st) {
+                       int32_t *ycol, float *yval, int32_t *ycnt, int32_t *fb,
+                       const int32_t *failed, int grid, size_t lds, hipStream_t st) {
   hipLaunchKernelGGL(k_mcl_rows<G>, dim3(grid), dim3(MGeom<G>::WG), lds, st, dpr, rows, hdr, bin,
-                     lS, TT, mul, maxwin, r, rpost, prune, topk, cap, ycol, yval, ycnt, fb);
+                     lS, TT, mul, maxwin, r, rpost, prune, topk, cap, ycol, yval, ycnt, fb, failed);
 }
 
 size_t mcl_lds_bytes(int b, int G) {
@@ -742,8 +1014,19 @@ hipError_t launch_mcl(const Problem *dpr, const BinPlan &bp, const WsLayout &L, 
   int32_t *fb = reinterpret_cast<int32_t *>(ws + L.fbrows);
   const DevInfo &D = dev_info();
   const int maxwin = bp.maxwin < kTail ? bp.maxwin : kTail;
+  double *rabs = reinterpret_cast<double *>(ws + L.mcl_rabs);
+  // rows given back per bin: the binning's histograms are no longer needed
+  int32_t *failed = reinterpret_cast<int32_t *>(ws + L.blockhist);
+  hipLaunchKernelGGL(k_row_abs, dim3(D.cus * 8), dim3(256), 0, st, dpr, hdr, rabs, failed);
   for (int b = 1; b <= bp.maxbin; ++b) {
     if (bp.known && bp.count[b] == 0) continue;
+    // a row of this many products may fall on few columns
+    const bool few = b >= kFewBin;
+    if (few) {
+      const int grid = bp.known ? std::min(D.cus * 8, bp.count[b]) : D.cus * 8;
+      hipLaunchKernelGGL(k_mcl_few, dim3(grid), dim3(kFewNT), 0, st, dpr, rows, hdr, b, r, rpost,
+                         prune, topk, cap, rabs, pcol, pval, ycnt, failed);
+    }
     int G = bp.lanes[b] < 8 ? 8 : bp.lanes[b];  // no one-thread-per-row MCL kernel
     while (G < 1024 && mcl_lds_bytes(b, G) > D.lds_per_block) G *= 2;
     // a bin past the largest table that fits takes that table (rows whose
@@ -764,7 +1047,7 @@ hipError_t launch_mcl(const Problem *dpr, const BinPlan &bp, const WsLayout &L, 
     while ((1 << lS) < S) ++lS;
     switch (G) {
 #define SPG_MCL_CASE(g) \
-  case g: mcl_launch<g>(dpr, rows, hdr, b, lS, TT, mul, maxwin, r, rpost, prune, topk, cap, pcol, pval, ycnt, fb, grid, lds, st); break;
+  case g: mcl_launch<g>(dpr, rows, hdr, b, lS, TT, mul, maxwin, r, rpost, prune, topk, cap, pcol, pval, ycnt, fb, few ? failed : nullptr, grid, lds, st); break;
       SPG_MCL_CASE(8)
       SPG_MCL_CASE(16)
       SPG_MCL_CASE(32)
@@ -772,7 +1055,7 @@ hipError_t launch_mcl(const Problem *dpr, const BinPlan &bp, const WsLayout &L, 
       SPG_MCL_CASE(128)
       SPG_MCL_CASE(256)
       SPG_MCL_CASE(512)
-      default: mcl_launch<1024>(dpr, rows, hdr, b, lS, TT, mul, maxwin, r, rpost, prune, topk, cap, pcol, pval, ycnt, fb, grid, lds, st);
+      default: mcl_launch<1024>(dpr, rows, hdr, b, lS, TT, mul, maxwin, r, rpost, prune, topk, cap, pcol, pval, ycnt, fb, few ? failed : nullptr, grid, lds, st);
 #undef SPG_MCL_CASE
     }
   }
@@ -780,8 +1063,6 @@ hipError_t launch_mcl(const Problem *dpr, const BinPlan &bp, const WsLayout &L, 
     // heavy bins plus rows handed over by the LDS kernels
     // one 1024-thread block per CU (its register use allows no second one)
     const int grid = std::min(mcl_heavy_slots(bp.n), D.cus);
-    double *rabs = reinterpret_cast<double *>(ws + L.mcl_rabs);
-    hipLaunchKernelGGL(k_row_abs, dim3(D.cus * 8), dim3(256), 0, st, dpr, hdr, rabs);
     const size_t lds = (size_t)kPanel * 8 + (size_t)kPanel / 8;
     hipLaunchKernelGGL(k_mcl_panel, dim3(grid), dim3(kPT), lds, st, dpr, rows, hdr, bp.maxbin + 1,
                        r, rpost, prune, topk, cap, rabs, ws + L.mcl_slots, mcl_slot_bytes(bp.n), fb,

@@ -1,0 +1,76 @@
+"""GPU parity of Markov-clustering rows that fall on few columns: clusters of
+various sizes under random labels (up to and past the 512 columns that one
+block holds), rows with thousands of columns between them, top-k cuts, ties,
+no prune, both step orders, against the FP64 oracle step by step."""
+import numpy as np
+import pytest
+
+from mcl_check import check_mcl_step
+from paper_2603_21444_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+def _clusters(sizes, seed, weights="u", spread=0):
+    """Row-stochastic X whose clusters hold sizes[c] vertices each (labels
+    shuffled); the first `spread` rows hold 60 random columns instead."""
+    n = int(sum(sizes))
+    rng = synth.rng_for(seed, 2)
+    label = rng.permutation(n)
+    rows = [None] * n
+    base = 0
+    for c in sizes:
+        members = np.sort(label[base:base + c])
+        for v in label[base:base + c]:
+            rows[v] = members
+        base += c
+    for v in range(spread):
+        rows[v] = np.sort(rng.choice(n, size=60, replace=False))
+    w = [np.ones(r.size) if weights == "equal" else 0.5 + 0.5 * rng.random(r.size) for r in rows]
+    ip = np.concatenate([[0], np.cumsum([r.size for r in rows])]).astype(np.int64)
+    return synth.HostCSR((n, n), ip, np.concatenate(rows).astype(np.int32),
+                         np.concatenate([x / x.sum() for x in w]).astype(np.float32))
+
+
+def _run(X, **kw):
+    import torch
+    from paper_2603_21444_amd import binding
+    plan = binding.Plan()
+    got = binding.mcl_iteration(binding.to_device(X), plan=plan, **kw)
+    torch.cuda.synchronize()
+    assert plan.status() == binding.SPG_OK
+    return got.to_host()
+
+
+@pytest.mark.parametrize("order,prune,topk", [("workload", 1e-4, 1000), ("workload", 0.0, 30),
+                                              ("paper", 1e-3, 500), ("paper", 0.0, 7)])
+def test_clusters_of_many_sizes(order, prune, topk):
+    sizes = [17, 20, 33, 64, 90, 128, 200] * 6 + [40] * 30
+    X = _clusters(sizes, 3)
+    check_mcl_step(X, _run(X, r=2, prune=prune, topk=topk, order=order), 2, prune, topk, order=order)
+
+
+def test_rows_at_the_limit_of_columns():
+    """512 columns are held, 513 are given back; both in one bin with rows
+    that are given back for having thousands."""
+    X = _clusters([512, 513, 511, 100, 30, 30, 30], 5, spread=150)
+    check_mcl_step(X, _run(X, r=2, prune=1e-5, topk=1000), 2, 1e-5, 1000)
+
+
+@pytest.mark.parametrize("topk", [1, 5, 64])
+def test_ties_keep_the_smallest_columns(topk):
+    X = _clusters([64, 128, 32] * 4, 7, weights="equal")
+    got = _run(X, r=2, prune=1e-4, topk=topk)
+    lens = np.diff(X.indptr)
+    for i in range(X.shape[0]):
+        k = min(topk, int(lens[i]))
+        c, v = got.row(i)
+        assert np.array_equal(c, X.row(i)[0][:k]), i
+        assert np.allclose(v, 1.0 / k, rtol=1e-6)
+
+
+def test_many_rows_given_back():
+    """Most rows have more columns than a block holds: after the first
+    hundreds the rest of the bin is left to the hash kernel."""
+    X = _clusters([25] * 200, 9, spread=4000)
+    check_mcl_step(X, _run(X, r=2, prune=1e-6, topk=4000), 2, 1e-6, 4000, rows=np.arange(0, 5000, 3))
