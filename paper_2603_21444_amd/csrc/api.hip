@@ -93,6 +93,7 @@ const DevInfo &dev_info() {
   (void)configure_mcl_lds(d.lds_per_block);
   (void)configure_split_lds(d.lds_per_block);
   (void)configure_wave_lds(d.lds_per_block);
+  (void)configure_block_lds(d.lds_per_block);
   (void)hipGetLastError();
   if (g_ndev == kMaxDevices) {  // more devices than the table: reuse the last entry
     g_dev[kMaxDevices - 1] = d;

@@ -126,6 +126,16 @@ void launch_num_sort(const Problem *dpr, const int32_t *rows, WsHeader *hdr, int
                      const int32_t *crp, int32_t *ccol, void *cval, bool f64, int32_t *fb,
                      hipStream_t st);
 
+// Rows of one block each, at most eight products per thread.
+bool block_rows_ok(int b, int lanes, int64_t n, size_t vbytes);
+void launch_num_block(const Problem *dpr, const int32_t *rows, WsHeader *hdr, int bin, int lanes,
+                      int count, int n, const int32_t *crp, int32_t *ccol, void *cval, bool f64,
+                      int32_t *fb, hipStream_t st);
+bool sym_block_ok(int b, int lanes);
+void launch_sym_block(const Problem *dpr, const int32_t *rows, WsHeader *hdr, int bin, int lanes,
+                      int count, int32_t *cnt, hipStream_t st);
+hipError_t configure_block_lds(size_t lds_max);
+
 // One thread per row for bin 1 (at most 16 products per row): tuning lanes
 // value 1 selects these kernels.
 void launch_sym_tiny(const Problem *dpr, const int32_t *rows, const WsHeader *hdr, int bin,

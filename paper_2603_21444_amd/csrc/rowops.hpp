@@ -27,6 +27,36 @@ __device__ __forceinline__ uint64_t lanes_below() {
   return lane == 0 ? 0ull : (~0ull >> (kWave - lane));
 }
 
+// v of the lane that the DPP control names (0 where that is outside the row
+// of 16 lanes or, with a row mask, in the rows left out).
+template <int CTRL, int ROWS = 0xf>
+__device__ __forceinline__ uint32_t dpp(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xf, true);
+}
+
+// Inclusive prefix sum over the G lanes of a group.
+template <int G>
+__device__ __forceinline__ int group_incl_scan(int v) {
+  v += (int)dpp<0x111>((uint32_t)v);  // row_shr 1, 2, 4, 8
+  v += (int)dpp<0x112>((uint32_t)v);
+  v += (int)dpp<0x114>((uint32_t)v);
+  v += (int)dpp<0x118>((uint32_t)v);
+  if (G >= 32) v += (int)dpp<0x142, 0xa>((uint32_t)v);  // row_bcast 15 into rows 1, 3
+  if (G >= 64) v += (int)dpp<0x143, 0xc>((uint32_t)v);  // row_bcast 31 into rows 2, 3
+  return v;
+}
+
+// The largest of the wave's values (non-negative), in its last lane.
+__device__ __forceinline__ int wave_max_last(int v) {
+  v = max(v, (int)dpp<0x111>((uint32_t)v));
+  v = max(v, (int)dpp<0x112>((uint32_t)v));
+  v = max(v, (int)dpp<0x114>((uint32_t)v));
+  v = max(v, (int)dpp<0x118>((uint32_t)v));
+  v = max(v, (int)dpp<0x142, 0xa>((uint32_t)v));
+  v = max(v, (int)dpp<0x143, 0xc>((uint32_t)v));
+  return v;
+}
+
 // Exclusive prefix sum of v over the group's lanes (l = lane in group);
 // `total` gets the group sum.  BLOCK groups use wtot[blockDim/64] in LDS.
 template <bool BLOCK, int G>
