@@ -298,6 +298,26 @@ BinPlan make_binplan(spg_plan p, int maxbin, bool counts_known, const int *count
   return bp;
 }
 
+// Whether B's columns and values are worth laying side by side (k_pair_b):
+// every A entry then gathers one line less, and an entry of B costs 16 bytes
+// once.  An aggregation operator (16 A entries per B entry, 2^20 x 2^17)
+// gains, 1.13 -> 0.93 ms; with as many A entries as B entries unstructured
+// rows still do (2^20 rows of 16 x 16: 2.02 -> 1.93 ms), but rows in bands or
+// with hubs, whose lines stay in the caches, lose (2.06 -> 2.21, R-MAT stages
+// 6.88 -> 7.07 ms), so the line lies at twice as many.  Not for sums (each
+// operand row is read once), nor for operands that stay in an L2 of 4 MB.
+// The words take up to an eighth of the heavy rows' region.  Returns the
+// bytes, 0 for none.
+size_t pair_bytes(int K, const spg_csr *A, const spg_csr *B) {
+  if (!A) return 0;
+  int64_t na = 0, nb = 0;
+  for (int k = 0; k < K; ++k) {
+    na += A[k].nnz;
+    nb += B[k].nnz;
+  }
+  return na >= 2 * nb && nb * 8 >= (4 << 20) ? (size_t)nb * 8 : 0;
+}
+
 // Shared symbolic sequence for products (identity == false) and merges.
 int run_symbolic(spg_plan p, const Problem &pr, const spg_csr *A, const spg_csr *B,
                  int32_t *C_row_ptr, int64_t *C_nnz_host, int64_t capacity, void *workspace,
@@ -306,8 +326,20 @@ int run_symbolic(spg_plan p, const Problem &pr, const spg_csr *A, const spg_csr 
   const int heavy = heavy_override > 0         ? heavy_override
                     : p->tun.heavy_slots > 0 ? p->tun.heavy_slots
                                              : default_heavy_slots(n);
-  const WsLayout L = ws_layout(m, n, heavy);
+  WsLayout L = ws_layout(m, n, heavy);
   if (!workspace || ws_bytes < L.total) return SPG_ERR_WORKSPACE;
+  if (const size_t pb = pair_bytes(pr.K, A, B)) {
+    // fewer concurrent heavy rows make room for the words behind the layout
+    const size_t slot = (size_t)(std::max(n, 1) + 4) * 8;
+    const size_t less = (pb + slot - 1) / slot;
+    if (less <= (size_t)heavy / 8) {
+      const WsLayout S = ws_layout(m, n, heavy - (int)less);
+      if (S.total + pb <= ws_bytes) {
+        L = S;
+        L.pairs = S.total;
+      }
+    }
+  }
   if (!C_nnz_host && capacity < 0) return SPG_ERR_ARG;
   const bool eager = C_nnz_host != nullptr;
   const bool clear = eager || p->status_ws != workspace;
@@ -444,7 +476,7 @@ bool same_operands(spg_plan p, int K, const spg_csr *A, const spg_csr *B) {
   return true;
 }
 
-int run_numeric(spg_plan p, const Problem &pr, spg_dtype dtype, int32_t *C_col_idx,
+int run_numeric(spg_plan p, Problem &pr, spg_dtype dtype, int32_t *C_col_idx,
                 void *C_vals, hipStream_t st) {
   if (dtype != SPG_F32 && dtype != SPG_F64) return SPG_ERR_ARG;
   if (p->counts_known && p->nnz > 0 && (!C_col_idx || !C_vals)) return SPG_ERR_ARG;
@@ -452,10 +484,24 @@ int run_numeric(spg_plan p, const Problem &pr, spg_dtype dtype, int32_t *C_col_i
   char *ws = p->ws;
   WsHeader *hdr = reinterpret_cast<WsHeader *>(ws);
   Problem *dpr = reinterpret_cast<Problem *>(ws + p->L.problem);
+  if (dtype == SPG_F32 && p->L.pairs) {
+    size_t o = p->L.pairs;
+    for (int k = 0; k < p->K; ++k) {
+      pr.part[k].pair = reinterpret_cast<const unsigned long long *>(ws + o);
+      o += (size_t)p->bnnz[k] * 8;
+    }
+  }
   hipError_t e = launch_setup(pr, dpr, hdr, false, false, st, split_ctl(p->L, ws));
   if (e != hipSuccess) return SPG_ERR_HIP;
   const int maxbin = dtype == SPG_F64 ? D.num_maxbin_f64 : D.num_maxbin_f32;
   BinPlan bp = make_binplan(p, maxbin, p->counts_known, p->num_count);
+  if (pr.part[0].pair) {
+    PairArgs a{};
+    for (int k = 0; k < p->K; ++k) a.nnz[k] = p->bnnz[k];
+    bp.pair = true;
+    e = launch_pair_b(dpr, a, hdr, st);
+    if (e != hipSuccess) return SPG_ERR_HIP;
+  }
   e = launch_numeric(dpr, bp, p->L, ws, p->crp, C_col_idx, C_vals, (int)dtype, st);
   p->stream = st;
   return hip_status(e);

@@ -59,6 +59,8 @@ struct Part {
   const void *aval;
   const int32_t *brp, *bcol;
   const void *bval;
+  // column (low half) and value bits of every B entry in one word (k_pair_b)
+  const unsigned long long *pair;
   int32_t a_identity;
   int32_t kdim;
 };

@@ -30,6 +30,7 @@ struct WsLayout {
   // split heavy rows (staging in the heavy accumulator region); split_F == 0: off
   size_t split_ctl = 0, split_rows = 0, split_fo = 0, split_cur = 0, split_segs = 0,
          split_items = 0;
+  size_t pairs = 0;  // words of B's columns and values (0: none)
   int split_F = 0, split_hmax = 0, split_segcap = 0, split_itemcap = 0;
   int64_t split_pcap = 0;
   size_t mcl_rabs = 0, mcl_slots = 0;  // MCL only: row sums of |x|, heavy-row slots
@@ -60,11 +61,18 @@ struct BinPlan {
   int heavy_slots = 1;
   int m = 0;  // rows
   int n = 0;
+  bool pair = false;  // Part::pair holds B's columns and values
   int maxwin = 32;
 };
 
 hipError_t launch_setup(const Problem &pr, Problem *dst, WsHeader *hdr, bool reset,
                         bool clear_status, hipStream_t st, SplitCtl *sc = nullptr);
+// Fills Part::pair of every part of `pr` (already set) with nnz[k] words.
+struct PairArgs {
+  int64_t nnz[SPG_MAX_PARTS];
+};
+hipError_t launch_pair_b(const Problem *dpr, const PairArgs &a, const WsHeader *hdr,
+                         hipStream_t st);
 hipError_t launch_clear_status(WsHeader *hdr, hipStream_t st);
 hipError_t launch_validate(const int32_t *rp, const int32_t *col, int rows, int ncols,
                            int64_t nnz, WsHeader *hdr, hipStream_t st);
@@ -123,7 +131,7 @@ hipError_t launch_permute(const spg_csr &A, const int32_t *prow, const int32_t *
 // Rows of at most 1024 products, sorted in the registers of 16 to 64 lanes.
 bool sort_rows_ok(int b, int64_t n);
 void launch_num_sort(const Problem *dpr, const int32_t *rows, WsHeader *hdr, int bin, int count,
-                     const int32_t *crp, int32_t *ccol, void *cval, bool f64, int32_t *fb,
+                     bool pair, const int32_t *crp, int32_t *ccol, void *cval, bool f64, int32_t *fb,
                      hipStream_t st);
 
 // Rows of one block each, at most eight products per thread.

@@ -926,7 +926,7 @@ static hipError_t numeric_impl(const Problem *dpr, const BinPlan &bp, const WsLa
       continue;
     }
     if (sort_rows_ok(b, bp.n)) {
-      launch_num_sort(dpr, rows, hdr, b, bins_count(bp, b, b), crp, ccol, cval, sizeof(VT) == 8,
+      launch_num_sort(dpr, rows, hdr, b, bins_count(bp, b, b), bp.pair, crp, ccol, cval, sizeof(VT) == 8,
                       fb, st);
       continue;
     }

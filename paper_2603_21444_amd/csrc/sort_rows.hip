@@ -177,10 +177,11 @@ struct SortLds {
 // The products of one chunk of at most G entries (lane l: entry l; length 0:
 // none), the first of them product `base` of the row.  Returns the number
 // of products so far.
-template <int G, int E, typename VT>
+template <int G, int E, bool PAIR, typename VT>
 __device__ __forceinline__ int sort_chunk(SortLds<G, E, VT> &s, const SPG_GLOBAL int32_t *bcol,
-                                          const SPG_GLOBAL VT *bval, int l, int b0, int len, VT a,
-                                          int base, uint32_t (&key)[E]) {
+                                          const SPG_GLOBAL VT *bval,
+                                          const SPG_GLOBAL unsigned long long *pair, int l, int b0,
+                                          int len, VT a, int base, uint32_t (&key)[E]) {
   constexpr int CAP = G * E, W = (CAP + 31) / 32, IB = ilog2(CAP);
   static_assert(W <= G, "one lane clears one word of the marks");
   if (l < W) s.mark[l] = 0u;
@@ -230,11 +231,20 @@ __device__ __forceinline__ int sort_chunk(SortLds<G, E, VT> &s, const SPG_GLOBAL
     for (int t = 0; t < E; ++t) en[t] = s.entry[e[t]];
     int col[E];
     VT bv[E];
+    if constexpr (PAIR) {
 #pragma unroll
-    for (int t = 0; t < E; ++t) {
-      const int q = en[t].b + (in[t] ? t * G + l : base);
-      col[t] = bcol[q];
-      bv[t] = bval[q];
+      for (int t = 0; t < E; ++t) {
+        const unsigned long long w = pair[en[t].b + (in[t] ? t * G + l : base)];
+        col[t] = (int)(uint32_t)w;
+        bv[t] = (VT)__uint_as_float((uint32_t)(w >> 32));
+      }
+    } else {
+#pragma unroll
+      for (int t = 0; t < E; ++t) {
+        const int q = en[t].b + (in[t] ? t * G + l : base);
+        col[t] = bcol[q];
+        bv[t] = bval[q];
+      }
     }
 #pragma unroll
     for (int t = 0; t < E; ++t) {
@@ -281,7 +291,8 @@ struct SortNext {
 template <int G, int E>
 constexpr int sort_waves() { return E > 4 ? 4 : (E == 4 && G < kWave ? 6 : 8); }
 
-template <int G, int E, typename VT>
+// PAIR: B read as words of column and FP32 value (Part::pair).
+template <int G, int E, bool PAIR, typename VT>
 __global__ __launch_bounds__(256, (sort_waves<G, E>())) void k_num_sort(
     const Problem *__restrict__ pr, const int32_t *__restrict__ rows, WsHeader *__restrict__ hdr,
     int bin, const int32_t *__restrict__ crp, int32_t *__restrict__ ccol, VT *__restrict__ cval,
@@ -295,6 +306,9 @@ __global__ __launch_bounds__(256, (sort_waves<G, E>())) void k_num_sort(
   const int32_t *list = rows + hdr->bin_start[bin];
   const int stride = gridDim.x * R;
   const Part &P0 = pr->part[0];
+  const SPG_GLOBAL int32_t *bcol0 = gp(P0.bcol);
+  const SPG_GLOBAL VT *bval0 = gp(static_cast<const VT *>(P0.bval));
+  const SPG_GLOBAL unsigned long long *pair0 = PAIR ? gp(P0.pair) : nullptr;
   const int K = pr->K;
   int ri = blockIdx.x * R + slot;
   // a wave runs while any of its groups has a row
@@ -316,8 +330,7 @@ __global__ __launch_bounds__(256, (sort_waves<G, E>())) void k_num_sort(
     uint32_t key[E];
 #pragma unroll
     for (int t = 0; t < E; ++t) key[t] = 0xffffffffu;
-    int P = sort_chunk<G, E, VT>(s, gp(P0.bcol), gp(static_cast<const VT *>(P0.bval)), l, b0, len,
-                                 n0.a, 0, key);
+    int P = sort_chunk<G, E, PAIR, VT>(s, bcol0, bval0, pair0, l, b0, len, n0.a, 0, key);
     b0 = len = 0;  // the next row's first entries
     if (n1.r >= 0) {
       b0 = gp(P0.brp)[n1.r];
@@ -345,8 +358,8 @@ __global__ __launch_bounds__(256, (sort_waves<G, E>())) void k_num_sort(
           cl = gp(Pk.brp)[r + 1] - cb;
         }
         P = min(P, CAP + 1);
-        P = sort_chunk<G, E, VT>(s, gp(Pk.bcol), gp(static_cast<const VT *>(Pk.bval)), l, cb, cl,
-                                 a, P, key);
+        P = sort_chunk<G, E, PAIR, VT>(s, gp(Pk.bcol), gp(static_cast<const VT *>(Pk.bval)),
+                                       gp(Pk.pair), l, cb, cl, a, P, key);
         as += G;
       }
     }
@@ -432,39 +445,46 @@ bool sort_rows_ok(int b, int64_t n) {
 
 template <int G, int E, typename VT>
 static void num_sort(const Problem *dpr, const int32_t *rows, WsHeader *hdr, int bin, int count,
-                     const int32_t *crp, int32_t *ccol, VT *cval, int32_t *fb, hipStream_t st) {
+                     bool pair, const int32_t *crp, int32_t *ccol, VT *cval, int32_t *fb, hipStream_t st) {
   const DevInfo &D = dev_info();
   constexpr int R = 256 / G;
   const int by_waves = sort_waves<G, E>();
   const int by_lds = (int)(D.lds_per_cu / (sizeof(SortLds<G, E, VT>) * R));
   int grid = D.cus * std::max(1, std::min(by_waves, by_lds));
   if (count >= 0) grid = std::min(grid, (count + R - 1) / R);
-  hipLaunchKernelGGL((k_num_sort<G, E, VT>), dim3(std::max(1, grid)), dim3(256), 0, st, dpr, rows,
-                     hdr, bin, crp, ccol, cval, fb);
+  if constexpr (sizeof(VT) == 4) {
+    if (pair) {
+      hipLaunchKernelGGL((k_num_sort<G, E, true, VT>), dim3(std::max(1, grid)), dim3(256), 0, st,
+                         dpr, rows, hdr, bin, crp, ccol, cval, fb);
+      return;
+    }
+  }
+  hipLaunchKernelGGL((k_num_sort<G, E, false, VT>), dim3(std::max(1, grid)), dim3(256), 0, st, dpr,
+                     rows, hdr, bin, crp, ccol, cval, fb);
 }
 
 template <typename VT>
 static void num_sort_bin(const Problem *dpr, const int32_t *rows, WsHeader *hdr, int bin,
-                         int count, const int32_t *crp, int32_t *ccol, VT *cval, int32_t *fb,
-                         hipStream_t st) {
+                         int count, bool pair, const int32_t *crp, int32_t *ccol, VT *cval,
+                         int32_t *fb, hipStream_t st) {
   switch (bin) {
-    case 1: num_sort<16, 1, VT>(dpr, rows, hdr, bin, count, crp, ccol, cval, fb, st); break;
-    case 2: num_sort<16, 2, VT>(dpr, rows, hdr, bin, count, crp, ccol, cval, fb, st); break;
-    case 3: num_sort<16, 4, VT>(dpr, rows, hdr, bin, count, crp, ccol, cval, fb, st); break;
-    case 4: num_sort<32, 4, VT>(dpr, rows, hdr, bin, count, crp, ccol, cval, fb, st); break;
-    case 5: num_sort<64, 4, VT>(dpr, rows, hdr, bin, count, crp, ccol, cval, fb, st); break;
-    case 6: num_sort<64, 8, VT>(dpr, rows, hdr, bin, count, crp, ccol, cval, fb, st); break;
-    default: num_sort<64, 16, VT>(dpr, rows, hdr, bin, count, crp, ccol, cval, fb, st); break;
+    case 1: num_sort<16, 1, VT>(dpr, rows, hdr, bin, count, pair, crp, ccol, cval, fb, st); break;
+    case 2: num_sort<16, 2, VT>(dpr, rows, hdr, bin, count, pair, crp, ccol, cval, fb, st); break;
+    case 3: num_sort<16, 4, VT>(dpr, rows, hdr, bin, count, pair, crp, ccol, cval, fb, st); break;
+    case 4: num_sort<32, 4, VT>(dpr, rows, hdr, bin, count, pair, crp, ccol, cval, fb, st); break;
+    case 5: num_sort<64, 4, VT>(dpr, rows, hdr, bin, count, pair, crp, ccol, cval, fb, st); break;
+    case 6: num_sort<64, 8, VT>(dpr, rows, hdr, bin, count, pair, crp, ccol, cval, fb, st); break;
+    default: num_sort<64, 16, VT>(dpr, rows, hdr, bin, count, pair, crp, ccol, cval, fb, st); break;
   }
 }
 
 void launch_num_sort(const Problem *dpr, const int32_t *rows, WsHeader *hdr, int bin, int count,
-                     const int32_t *crp, int32_t *ccol, void *cval, bool f64, int32_t *fb,
+                     bool pair, const int32_t *crp, int32_t *ccol, void *cval, bool f64, int32_t *fb,
                      hipStream_t st) {
   if (f64)
-    num_sort_bin<double>(dpr, rows, hdr, bin, count, crp, ccol, static_cast<double *>(cval), fb, st);
+    num_sort_bin<double>(dpr, rows, hdr, bin, count, pair, crp, ccol, static_cast<double *>(cval), fb, st);
   else
-    num_sort_bin<float>(dpr, rows, hdr, bin, count, crp, ccol, static_cast<float *>(cval), fb, st);
+    num_sort_bin<float>(dpr, rows, hdr, bin, count, pair, crp, ccol, static_cast<float *>(cval), fb, st);
 }
 
 }  // namespace spg
