@@ -564,23 +564,31 @@ __global__ __launch_bounds__(kFewNT, 8) void k_mcl_few(
 // that no partial sum can overflow; the rounding error of an entry is at most
 // (terms) * 2^-62 of that bound, far below the FP32 rounding of the result.
 //
-// After a panel, its present columns are inflated (p = v^r) and p is summed
-// into the row's running sum.  A column can only survive the prune if
-// p >= prune * (final sum) >= prune * (sum of the panels before), so only
-// such candidates are appended, in column order, to the row's list in the
-// slot scratch (capacity n).  At the end the list is filtered with the exact
-// test on p / sum, the top-k threshold is found by bisection on the float
-// bit patterns, ties go to the smaller columns (list order), and the result is
-// renormalised and written in column order.
+// After a panel, its columns are inflated (p = v^r) and p is summed into the
+// row's running sum.  A column can only survive the prune if p >= prune *
+// (final sum) >= prune * (sum of the panels before, or of the first one), so
+// only such candidates are appended, in column order, to the row's list in
+// the slot scratch (capacity n).  At the end the exact test on p / sum moves
+// the kept entries to LDS, the top-k threshold is found there by an eight-way
+// search on the float bit patterns, ties go to the smaller columns, and the
+// result is renormalised and written in column order.  (More kept entries
+// than a panel has columns, or none: the same on the list in place.)
+//
+// 2^17 rows of 400 entries (160000 products a row), per call: 136 -> 85 ms.
+// Of these the accumulation takes 55, bound by its reads (every panel reads
+// three lines per entry and array, 336 GB in all; generic pointers to the
+// entries' cursors made flat loads there, which waited for each other: 38 ms
+// more with them in the loop), the panels' ends 14 (30 with lanes 16 columns
+// apart, on two banks, and every value computed twice), the selection 16 (48
+// with a block-wide reduction per 1024 entries and bisection step).
 constexpr int kPanel = 16384;  // columns per panel: 128 KiB of int64 in LDS
 constexpr int kPT = 1024;      // threads of a heavy block
 constexpr int kCPT = kPanel / kPT;  // panel columns per thread in the epilogue
-// Entry groups a wave serves at once: six for rows whose entries have 32 or
-// more elements per panel (32 or 64 lanes per entry), four otherwise; more
-// groups spill past the 128 registers a 1024-thread block allows.
-constexpr int kPUDense = 6, kPUSparse = 4;
+// Entry groups a wave serves at once, for rows whose entries have 32 or more
+// elements per panel (32 or 64 lanes per entry) and for others (4, 6 and 8
+// groups for the first: 1 to 4 % slower).
+constexpr int kPUDense = 5, kPUSparse = 4;
 constexpr int kPE = 1024;     // entries whose cursors stay in LDS
-static_assert(kCPT == 16, "the epilogue reads one 16-bit half of a bitmap word per thread");
 
 struct PanelRed {
   double s;
@@ -618,7 +626,7 @@ __device__ __forceinline__ PanelRed panel_reduce(double s, int c, int mn, unsign
   // lane l (mod 16) picks up wave l's partials; a butterfly over 16 lanes
   // gives every lane the same totals (IEEE addition is commutative).
   constexpr int NW = kPT / kWave;
-  static_assert(NW == 16, "one partial per lane of a 16-lane segment");
+  static_assert(NW == 8 || NW == 16, "one partial per lane of a segment");
   const int l16 = lane & (NW - 1);
   double ts = rs[l16];
   int tt = rc[l16];
@@ -638,44 +646,53 @@ __device__ __forceinline__ PanelRed panel_reduce(double s, int c, int mn, unsign
   return PanelRed{ts, tt, tp + x - c, tm, tb};
 }
 
+// x rounded to the nearest integer (ties to even), |x| < 2^63.
+__device__ __forceinline__ unsigned long long round_i64(double x) {
+  const double y = rint(x);
+  const double hi = floor(y * 0x1p-32);
+  const double lo = fma(hi, -0x1p32, y);  // exact, in [0, 2^32)
+  return ((unsigned long long)(uint32_t)(int)hi << 32) | (uint32_t)lo;
+}
+
 // Adds the products of entries [0, nA) that fall in [plo, plo + width) and
-// advances their cursors; returns this lane's smallest next column.
-template <int kPU, typename CurT>
+// advances their cursors; returns this lane's smallest next column.  S = 2^LS
+// lanes per entry.  TRACK: also marks the columns in the bitmap.  The entry
+// arrays come as LDS or as global pointers: generic ones would make flat
+// loads, whose waits drain every load in flight.
+template <int kPU, int LS, bool TRACK, typename IP, typename EP, typename VP>
 __device__ __forceinline__ int panel_accumulate(const SPG_GLOBAL int32_t *bcol,
-                                                const SPG_GLOBAL float *bval, CurT *ecur,
-                                                const CurT *eend, const float *eval, int nA,
-                                                int lS, double sigma, int plo, uint32_t width,
-                                                unsigned long long *pacc, uint32_t *pbm) {
+                                                const SPG_GLOBAL float *bval, IP ecur, EP eend,
+                                                VP eval, int nA, double sigma, int plo,
+                                                uint32_t width, unsigned long long *pacc,
+                                                uint32_t *pbm) {
+  constexpr int S = 1 << LS, EPW = kWave >> LS;
   const int lane = lane_id(), w = threadIdx.x / kWave;
-  const int S = 1 << lS, EPW = kWave >> lS;
-  const int sub = lane >> lS, q = lane & (S - 1), base = sub << lS;
+  const int sub = lane >> LS, q = lane & (S - 1), base = sub << LS;
   const int phi = plo + kPanel;
   int tmn = INT32_MAX;
   for (int e0 = w * EPW * kPU; e0 < nA; e0 += (kPT / kWave) * EPW * kPU) {
     int c[kPU], en[kPU];
-    float a[kPU];
-    bool act[kPU];
+    double a[kPU];
     // Every read below uses an in-range index for every lane (entry 0; B
     // element 0, which exists since a heavy row has products), so the reads
     // of all kPU groups are issued before the first wait.
 #pragma unroll
     for (int u = 0; u < kPU; ++u) {
       const int e = e0 + u * EPW + sub;
-      act[u] = e < nA;
-      const int es = act[u] ? e : 0;
-      c[u] = (int)ecur[es];
-      en[u] = (int)eend[es];
-      a[u] = eval[es];
+      const int es = e < nA ? e : 0;
+      c[u] = ecur[es];
+      en[u] = e < nA ? eend[es] : 0;  // no entry: nothing left to read
+      a[u] = (double)eval[es] * sigma;
     }
-    bool more = true;
-    while (more) {
+    bool more;
+    do {
       int col[kPU];
       float v[kPU];
 #pragma unroll
       for (int u = 0; u < kPU; ++u) {
         const int idx = c[u] + q;
-        const bool ld = act[u] && idx < en[u];
-        const int li = ld ? idx : 0;
+        const bool ld = idx < en[u];
+        const uint32_t li = ld ? (uint32_t)idx : 0u;
         col[u] = bcol[li];
         v[u] = bval[li];
         col[u] = ld ? col[u] : INT32_MAX;
@@ -685,35 +702,75 @@ __device__ __forceinline__ int panel_accumulate(const SPG_GLOBAL int32_t *bcol,
       for (int u = 0; u < kPU; ++u) {
         const bool in = col[u] < phi;
         const uint32_t cl = (uint32_t)(col[u] - plo);
-        if (in && cl < width) {  // columns outside [0, n) are skipped
-          const long long qv = __double2ll_rn((double)a[u] * (double)v[u] * sigma);
-          atomicAdd(&pacc[cl], (unsigned long long)qv);
-          atomicOr(&pbm[cl >> 5], 1u << (cl & 31));
+        if (cl < width) {  // columns outside [0, n) are skipped
+          atomicAdd(&pacc[cl], round_i64(a[u] * (double)v[u]));
+          if (TRACK) atomicOr(&pbm[cl >> 5], 1u << (cl & 31));
         }
-        const uint64_t m = __ballot(in);
-        const int k = __popcll((m >> base) & (S == kWave ? ~0ull : ((1ull << S) - 1)));
-        // the group's lane k holds the entry's first column past the panel
-        // (INT32_MAX once its row ended, or for an inactive group); the
-        // block-wide minimum comes later, so that lane keeps it
-        if (q == k) tmn = min(tmn, col[u]);
-        if (act[u]) {
-          c[u] += k;
-          if (k < S) act[u] = false;  // the entry left the panel (or its row ended)
-        }
-        more = more || act[u];
+        const uint64_t m = __builtin_amdgcn_ballot_w64(in);
+        int k;
+        if (LS == 6) k = __popcll(m);
+        else if (LS == 5) k = lane < 32 ? __popc((uint32_t)m) : __popc((uint32_t)(m >> 32));
+        else k = __popc((uint32_t)(m >> base) & ((1u << (S & 31)) - 1u));
+        // the columns read past the panel start with the entry's next one
+        tmn = min(tmn, in ? INT32_MAX : col[u]);
+        c[u] += k;
+        if (k < S) en[u] = 0;  // the entry left the panel (or its row ended)
+        more = more || k == S;
       }
       more = __any(more);
-    }
+    } while (more);
 #pragma unroll
     for (int u = 0; u < kPU; ++u) {
       const int e = e0 + u * EPW + sub;
-      if (e < nA && q == 0) ecur[e] = (CurT)c[u];
+      if (e < nA && q == 0) ecur[e] = c[u];
     }
   }
   return tmn;
 }
 
-__global__ __launch_bounds__(kPT) void k_mcl_panel(
+// What a panel leaves behind: every thread owns 16 of its columns (lane l of
+// wave w: 1024 w + 64 j + l, so that a wave's reads hit all banks).  Values
+// below `low` are no candidates (TRACK: absent columns have none, NaN, and
+// the largest value's smallest column is kept).
+template <bool TRACK>
+__device__ __forceinline__ void panel_finish(unsigned long long *pacc, uint32_t *pbm, int plo,
+                                             double inv_sigma, int r, bool even, float low,
+                                             float (&pw)[kCPT], double &ps, int &cnt,
+                                             uint32_t &bbits, int &bcolumn) {
+  const int lane = lane_id(), c0 = threadIdx.x / kWave * (kCPT * kWave) + lane;
+  ps = 0.0;
+  cnt = 0;
+  constexpr int H = kCPT / 2;
+#pragma unroll
+  for (int j0 = 0; j0 < kCPT; j0 += H) {
+    unsigned long long acc[H];
+#pragma unroll
+    for (int j = 0; j < H; ++j) acc[j] = pacc[c0 + (j0 + j) * kWave];
+#pragma unroll
+    for (int j = 0; j < H; ++j) pacc[c0 + (j0 + j) * kWave] = 0ull;
+#pragma unroll
+    for (int j = 0; j < H; ++j) {
+      const int jj = j0 + j;
+      float p = ipow((float)((double)(long long)acc[j] * inv_sigma), r);
+      ps += (double)p;
+      if (TRACK) {
+        const bool present = pbm[(c0 + jj * kWave) >> 5] >> (lane & 31) & 1u;
+        const uint32_t bits = __float_as_uint(p);
+        if (present && (bits > bbits || bcolumn < 0)) {  // ties: the smaller column came first
+          bbits = bits;
+          bcolumn = plo + c0 + jj * kWave;
+        }
+        if (!present) p = __uint_as_float(0x7fc00000u);
+      } else if (!even) {
+        if (acc[j] == 0ull) p = __uint_as_float(0x7fc00000u);
+      }
+      pw[jj] = p;
+      cnt += __popcll(__ballot(p >= low));
+    }
+  }
+}
+
+__global__ __launch_bounds__(kPT, kPT / 256) void k_mcl_panel(
     const Problem *__restrict__ pr, const int32_t *__restrict__ rows, WsHeader *__restrict__ hdr,
     int blo, int r, int rpost, float prune, int topk, int cap, const double *__restrict__ rabs,
     char *__restrict__ scratch, size_t slot_bytes, const int32_t *__restrict__ fb_rows,
@@ -723,6 +780,7 @@ __global__ __launch_bounds__(kPT) void k_mcl_panel(
   __shared__ double rs[kPT / kWave];
   __shared__ int rc[kPT / kWave], rm[kPT / kWave];
   __shared__ unsigned long long rb[kPT / kWave];
+  __shared__ int kcnt[2 * 8 * (kPT / kWave)];  // counts of the top-k search
   __shared__ int s_cur[kPE], s_end[kPE];
   __shared__ float s_val[kPE];
   const int n = pr->n;
@@ -798,53 +856,254 @@ __global__ __launch_bounds__(kPT) void k_mcl_panel(
                          (double)((n + kPanel - 1) / kPanel);
       while (lS < 6 && (double)(1 << lS) < per) ++lS;
     }
-    int mnext = R.mn;
-    double scum = 0.0;
-    int nc = 0;
-    unsigned long long best = 0ull;
-    while (mnext < n) {
-      const int plo = mnext & ~(kPanel - 1);
-      const uint32_t width = plo < 0 ? 0u : (uint32_t)min(kPanel, n - plo);
-      const int tmn =
-          lS >= 5 ? panel_accumulate<kPUDense>(bcol, bval, ccur, cend, cval, nA, lS, sigma, plo,
-                                               width, pacc, pbm)
-                  : panel_accumulate<kPUSparse>(bcol, bval, ccur, cend, cval, nA, lS, sigma, plo,
-                                                width, pacc, pbm);
-      __syncthreads();
-      // epilogue of the panel: thread tid owns columns plo + 16 tid .. + 15
-      const double thr = even ? (double)prune * scum * (1.0 - 1.0 / 1024.0) : -HUGE_VAL;
-      const uint32_t bits = (pbm[tid >> 1] >> ((tid & 1) * 16)) & 0xffffu;
-      double ps = 0.0;
-      int cnt = 0;
-      for (uint32_t b = bits; b; b &= b - 1) {
-        const int cl = tid * kCPT + __ffs(b) - 1;
-        const float pw = ipow((float)((double)(long long)pacc[cl] * inv_sigma), r);
-        ps += (double)pw;
-        const unsigned long long key = vc_key(pw, plo + cl);
-        best = key > best ? key : best;
-        cnt += (double)pw >= thr ? 1 : 0;
-      }
-      R = panel_reduce(ps, cnt, tmn, 0ull, rs, rc, rm, rb);
-      int o = nc + R.excl;
-      for (uint32_t b = bits; b; b &= b - 1) {
-        const int cl = tid * kCPT + __ffs(b) - 1;
-        const float pw = ipow((float)((double)(long long)pacc[cl] * inv_sigma), r);
-        pacc[cl] = 0ull;
-        if ((double)pw >= thr) {
-          lcol[o] = plo + cl;
-          lval[o] = pw;
-          ++o;
+    // The bitmap is kept only where it matters: with a prune above zero a
+    // column whose sum is zero is dropped like an absent one.  A row of
+    // which nothing is left is taken once more, with it.
+    const int mfirst = R.mn;
+    double scum;
+    float S;
+    int nc, nk, kept0;
+    uint32_t bbits;
+    int bcolumn;
+    bool track = !(prune > 0.f);
+    while (true) {
+      int mnext = mfirst;
+      scum = 0.0;
+      nc = 0;
+      bbits = 0u;
+      bcolumn = -1;
+      while (mnext < n) {
+        const int plo = mnext & ~(kPanel - 1);
+        const uint32_t width = plo < 0 ? 0u : (uint32_t)min(kPanel, n - plo);
+#define SPG_ACC(PU, LS, TRACK)                                                              \
+  panel_accumulate<PU, LS, TRACK>(bcol, bval, s_cur, s_end, s_val, nA, sigma, plo, width, pacc, \
+                                  pbm)
+#define SPG_ACC_G(PU, LS)                                                                     \
+  panel_accumulate<PU, LS, true>(bcol, bval, gpw(ecur), gpw(eend), gpw(evalg), nA, sigma, plo, \
+                                 width, pacc, pbm)
+        int tmn;
+        if (!lds_state) {  // the bitmap does no harm where it is not needed
+          tmn = lS >= 5 ? SPG_ACC_G(kPUDense, 5) : SPG_ACC_G(kPUSparse, 3);
+        } else if (track) {
+          tmn = lS >= 5 ? SPG_ACC(kPUDense, 5, true) : SPG_ACC(kPUSparse, 3, true);
+        } else {
+          switch (lS) {
+            case 6: tmn = SPG_ACC(kPUDense, 6, false); break;
+            case 5: tmn = SPG_ACC(kPUDense, 5, false); break;
+            case 4: tmn = SPG_ACC(kPUSparse, 4, false); break;
+            case 3: tmn = SPG_ACC(kPUSparse, 3, false); break;
+            default: tmn = SPG_ACC(kPUSparse, 2, false); break;
+          }
         }
+#undef SPG_ACC_G
+#undef SPG_ACC
+        __syncthreads();
+        // a product that is zero cannot survive a prune above zero
+        const float thr = (float)((double)prune * scum * (1.0 - 1.0 / 1024.0));
+        float low = !even ? -INFINITY : track ? thr : fmaxf(thr, 0x1p-149f);
+        float pw[kCPT];
+        double ps;
+        int cnt;
+        if (track)
+          panel_finish<true>(pacc, pbm, plo, inv_sigma, r, even, low, pw, ps, cnt, bbits, bcolumn);
+        else
+          panel_finish<false>(pacc, pbm, plo, inv_sigma, r, even, low, pw, ps, cnt, bbits, bcolumn);
+        if (even && !track && scum == 0.0) {
+          // the first sums: the row's sum is at least theirs
+          R = panel_reduce(ps, 0, INT32_MAX, 0ull, rs, rc, rm, rb);
+          low = fmaxf((float)((double)prune * R.s * (1.0 - 1.0 / 1024.0)), 0x1p-149f);
+          cnt = 0;
+#pragma unroll
+          for (int j = 0; j < kCPT; ++j) cnt += __popcll(__ballot(pw[j] >= low));
+          __syncthreads();
+        }
+        // the wave's candidates follow those of the waves before it (count 0
+        // in all lanes but one)
+        R = panel_reduce(ps, lane_id() == kWave - 1 ? cnt : 0, tmn, 0ull, rs, rc, rm, rb);
+        if (track || !lds_state)
+          for (int wd = tid; wd < kPanel / 32; wd += kPT) pbm[wd] = 0u;
+        int o = nc + __shfl(R.excl, 0);
+        const int c0 = plo + tid / kWave * (kCPT * kWave) + lane_id();
+#pragma unroll
+        for (int j = 0; j < kCPT; ++j) {
+          const uint64_t m = __ballot(pw[j] >= low);
+          if (pw[j] >= low) {
+            const int at = o + mbcnt(m);
+            lcol[at] = c0 + j * kWave;
+            lval[at] = pw[j];
+          }
+          o += __popcll(m);
+        }
+        scum += R.s;
+        nc += R.total;
+        mnext = R.mn;
+        // rs, rc, rm are rewritten, and the bitmap marked again, only after
+        // the next panel's first barrier, or that of the code below
+        if (track || !lds_state) __syncthreads();
       }
-      if ((tid & 1) == 0) pbm[tid >> 1] = 0u;
-      scum += R.s;
-      nc += R.total;
-      mnext = R.mn;
+      // values that the exact test keeps, per wave (a run of the list each)
+      __syncthreads();
+      S = (float)scum;
+      const int seg = ((nc + kPT - 1) / kPT) * kWave;
+      const int l0 = min(nc, tid / kWave * seg), l1 = min(nc, l0 + seg);
+      int mine = 0;
+      for (int t = l0; t < l1; t += kWave) {
+        const int idx = t + lane_id();
+        const bool keep = idx < l1 && !(lval[idx < l1 ? idx : l0] / S < prune);
+        mine += __popcll(__ballot(keep));
+      }
+      R = panel_reduce(0.0, lane_id() == kWave - 1 ? mine : 0, INT32_MAX, 0ull, rs, rc, rm, rb);
+      nk = R.total;
+      kept0 = __shfl(R.excl, 0);
+      if (track || (scum != 0.0 && nk > 0)) break;
+      // an emptied row, or one whose sums are all zero: its largest entry is
+      // wanted, and which columns are present matters
+      track = true;
+      __syncthreads();
+      for (int e = tid; e < nA; e += kPT) ccur[e] = gp(P.brp)[gp(P.acol)[as + e]];
       __syncthreads();
     }
-    // exact prune test on p / sum, compacting the list in place
-    const float S = (float)scum;
-    int nk = 0;
+    __syncthreads();
+    SPG_GLOBAL int32_t *cb = gpw(ycol) + (size_t)i * cap;
+    SPG_GLOBAL float *vb = gpw(yval) + (size_t)i * cap;
+    if (nk > 0 && nk <= kPanel) {
+      // the kept entries in LDS (column and value, in the panel's place)
+      {
+        const int seg = ((nc + kPT - 1) / kPT) * kWave;
+        const int l0 = min(nc, tid / kWave * seg), l1 = min(nc, l0 + seg);
+        int o = kept0;
+        for (int t = l0; t < l1; t += kWave) {
+          const int idx = t + lane_id();
+          const float q = idx < l1 ? lval[idx] / S + 0.f : 0.f;
+          const bool keep = idx < l1 && !(q < prune);
+          const uint64_t m = __ballot(keep);
+          if (keep)
+            pacc[o + mbcnt(m)] = (unsigned long long)(uint32_t)lcol[idx] |
+                                 ((unsigned long long)__float_as_uint(q) << 32);
+          o += __popcll(m);
+        }
+      }
+      __syncthreads();
+      // wave w: entries w seg .. w seg + seg - 1, 64 at a time
+      const int seg = ((nk + kPT - 1) / kPT) * kWave;
+      const int k0 = min(nk, tid / kWave * seg), k1 = min(nk, k0 + seg);
+      const uint32_t *bits_at = reinterpret_cast<const uint32_t *>(pacc) + 1;  // value of entry t: [2 t]
+      uint32_t tau = 0u;
+      int ties = 0, need = nk;  // ties at tau before this wave's; how many are kept
+      if (nk > topk) {
+        // the largest tau with at least topk values >= tau, by an eight-way
+        // search on the bit patterns (the values are >= 0): seven counts per
+        // step and wave, summed over the waves by every wave; two arrays in
+        // turn, so that a step needs one barrier
+        int step = 0;
+        auto count = [&](const uint32_t (&mid)[7], int (&total)[7]) {
+          int *slot = kcnt + (step++ & 1) * 8 * (kPT / kWave);
+          int cc[7] = {0, 0, 0, 0, 0, 0, 0};
+          for (int t = k0; t < k1; t += kWave) {
+            const int idx = t + lane_id();
+            const uint32_t v = idx < k1 ? bits_at[2 * idx] : 0u;
+#pragma unroll
+            for (int q = 0; q < 7; ++q) cc[q] += __popcll(__ballot(v >= mid[q]));
+          }
+          if (lane_id() == 0) {
+#pragma unroll
+            for (int q = 0; q < 7; ++q) slot[q * (kPT / kWave) + tid / kWave] = cc[q];
+          }
+          __syncthreads();
+          // lane l: counts of threshold l / 16 (two rounds), wave l % 16
+          const int x = group_incl_scan<16>(slot[lane_id()]);
+          const int y = group_incl_scan<16>(lane_id() < 48 ? slot[64 + lane_id()] : 0);
+#pragma unroll
+          for (int t = 0; t < 7; ++t)
+            total[t] = __builtin_amdgcn_readlane(t < 4 ? x : y, (t & 3) * 16 + 15);
+        };
+        static_assert(kPT / kWave == 16, "a row of 16 lanes holds the waves' counts");
+        uint32_t mid[7];
+        int total[7];
+        uint32_t lo = prune > 0.f ? __float_as_uint(prune) : 0u;
+        uint32_t hi = 0x7f800000u;
+        mid[0] = __float_as_uint(1.0625f) + 1u;  // a value is at most its row's sum
+#pragma unroll
+        for (int t = 1; t < 7; ++t) mid[t] = hi;
+        count(mid, total);
+        if (total[0] == 0) hi = mid[0] - 1u;
+        while (lo < hi) {  // tau in [lo, hi]
+          const uint32_t width8 = (hi - lo) / 8 + 1;
+#pragma unroll
+          for (int t = 0; t < 7; ++t) mid[t] = min(lo + (t + 1) * width8, hi + 1u);
+          count(mid, total);
+          uint32_t nhi = hi;
+#pragma unroll
+          for (int t = 6; t >= 0; --t)
+            if (total[t] < topk) nhi = mid[t] - 1u;
+          uint32_t nlo = lo;
+#pragma unroll
+          for (int t = 0; t < 7; ++t)
+            if (total[t] >= topk) nlo = mid[t];
+          lo = nlo;
+          hi = max(nhi, nlo);
+        }
+        tau = lo;
+        mid[0] = tau + 1u;
+        count(mid, total);
+        need = topk - total[0];  // ties at tau to keep, in column order
+        int tc = 0;
+        for (int t = k0; t < k1; t += kWave) {
+          const int idx = t + lane_id();
+          tc += __popcll(__ballot(idx < k1 && bits_at[2 * idx] == tau));
+        }
+        __syncthreads();
+        R = panel_reduce(0.0, lane_id() == kWave - 1 ? tc : 0, INT32_MAX, 0ull, rs, rc, rm, rb);
+        ties = __shfl(R.excl, 0);
+        __syncthreads();
+      }
+      // the selected entries: their sum, their number per wave
+      double s2 = 0.0;
+      int ns = 0;
+      auto selected = [&](int idx, uint32_t v, int &before) {
+        bool on = idx < k1;
+        if (nk > topk) {
+          const bool tie = on && v == tau;
+          const uint64_t m = __ballot(tie);
+          on = on && (v > tau || (tie && before + mbcnt(m) < need));
+          before += __popcll(m);
+        }
+        return on;
+      };
+      int before = ties;
+      for (int t = k0; t < k1; t += kWave) {
+        const int idx = t + lane_id();
+        const uint32_t v = idx < k1 ? bits_at[2 * idx] : 0u;
+        const bool on = selected(idx, v, before);
+        s2 += on ? (double)__uint_as_float(v) : 0.0;
+        ns += __popcll(__ballot(on));
+      }
+      R = panel_reduce(s2, lane_id() == kWave - 1 ? ns : 0, INT32_MAX, 0ull, rs, rc, rm, rb);
+      const float S2 = (float)R.s;
+      int o = __shfl(R.excl, 0);
+      before = ties;
+      for (int t = k0; t < k1; t += kWave) {
+        const int idx = t + lane_id();
+        const unsigned long long e = idx < k1 ? pacc[idx] : 0ull;
+        const bool on = selected(idx, (uint32_t)(e >> 32), before);
+        const uint64_t m = __ballot(on);
+        const int at = o + mbcnt(m);
+        if (on && at < cap) {
+          const float q = __uint_as_float((uint32_t)(e >> 32));
+          cb[at] = (int)(uint32_t)e;
+          vb[at] = rpost == 0 ? q / S2 : ipow(q, rpost);
+        }
+        o += __popcll(m);
+        if (idx < k1) pacc[idx] = 0ull;  // the panel starts clear
+      }
+      if (tid == 0) ycnt[i] = R.total < cap ? R.total : cap;
+      continue;
+    }
+    // none kept, or more than the panel holds (no prune): the list in place
+    const unsigned long long best = bcolumn < 0 ? 0ull
+                                                : ((unsigned long long)bbits << 32) |
+                                                      (uint32_t)(~(uint32_t)bcolumn);
+    nk = 0;
     for (int c0 = 0; c0 < nc; c0 += kPT) {
       const int idx = c0 + tid;
       int col = 0;
@@ -913,8 +1172,6 @@ __global__ __launch_bounds__(kPT) void k_mcl_panel(
     R = panel_reduce(s2, 0, INT32_MAX, 0ull, rs, rc, rm, rb);
     const float S2 = (float)R.s;
     __syncthreads();
-    SPG_GLOBAL int32_t *cb = gpw(ycol) + (size_t)i * cap;
-    SPG_GLOBAL float *vb = gpw(yval) + (size_t)i * cap;
     int outn = 0;
     if (nk == 0) {
       if (rowbest != 0ull) {  // emptied row: keep its largest entry
