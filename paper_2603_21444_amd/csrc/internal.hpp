@@ -130,6 +130,9 @@ hipError_t launch_permute(const spg_csr &A, const int32_t *prow, const int32_t *
 
 // Rows of at most 1024 products, sorted in the registers of 16 to 64 lanes.
 bool sort_rows_ok(int b, int64_t n);
+bool sym_sort_ok(int b);
+void launch_sym_sort(const Problem *dpr, const int32_t *rows, const WsHeader *hdr, int bin,
+                     int count, int32_t *cnt, hipStream_t st);
 void launch_num_sort(const Problem *dpr, const int32_t *rows, WsHeader *hdr, int bin, int count,
                      bool pair, const int32_t *crp, int32_t *ccol, void *cval, bool f64, int32_t *fb,
                      hipStream_t st);

@@ -838,6 +838,10 @@ hipError_t launch_symbolic_bins(const Problem *dpr, const BinPlan &bp, const WsL
       launch_sym_tiny(dpr, rows, hdr, b, bins_count(bp, b, b), bp.known, cnt, st);
       continue;
     }
+    if (sym_sort_ok(b)) {
+      launch_sym_sort(dpr, rows, hdr, b, bins_count(bp, b, b), cnt, st);
+      continue;
+    }
     if (G < 8) G = 8;
     if (G == kWave && sym_wave_lds_bytes(b) <= D.lds_per_block) {
       launch_sym_wave(dpr, rows, hdr, b, sub_log2(bp, b, G), bins_count(bp, b, b), cnt, st);
