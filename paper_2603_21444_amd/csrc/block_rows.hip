@@ -29,116 +29,11 @@
 // 0.20 + 0.11 ms.
 #include <algorithm>
 
+#include "block_ops.hpp"
 #include "internal.hpp"
 #include "rowops.hpp"
 
 namespace spg {
-
-constexpr int kBlkE = 8;  // products per thread
-// Rows with at most this many repeated products (products less distinct
-// columns) are ranked inside their buckets; rows with more sort them.
-constexpr int kDupList = 32;
-
-// Operand arrays of a block product, in LDS (lanes hold entries of several).
-template <typename VT>
-struct BlkPart {
-  const SPG_GLOBAL int32_t *arp, *acol, *brp, *bcol;
-  const SPG_GLOBAL VT *aval, *bval;
-};
-
-// An A entry with products: its value, its part, and its first B position
-// less the number of its first product.
-template <typename VT>
-struct BlkEntry {
-  VT a;
-  int b, k;
-};
-
-// What a thread holds of a row: the row, its place in C, the A entries per
-// part (lane k of each wave: part k) and its own entry.
-template <typename VT>
-struct BlkHead {
-  int i = -1, rs = 0, nnz = 0;
-  int as = 0, incl = 0, nA = 0;
-  int k = 0, r = -1, b0 = 0, len = 0;
-  VT a = VT(1);
-};
-
-template <typename VT>
-__device__ __forceinline__ void blk_parts(const BlkPart<VT> *part, int K, const int32_t *crp,
-                                          BlkHead<VT> &h) {
-  const int lane = lane_id();
-  h.as = 0;
-  int n = 0;
-  if (h.i >= 0) {
-    if (lane < K) {
-      const SPG_GLOBAL int32_t *arp = part[lane].arp;
-      if (arp) {
-        h.as = arp[h.i];
-        n = arp[h.i + 1] - h.as;
-      } else {  // identity: one entry, (i, 1)
-        n = 1;
-      }
-    }
-    if (crp) {
-      h.rs = __builtin_amdgcn_readfirstlane(gp(crp)[h.i]);
-      h.nnz = __builtin_amdgcn_readfirstlane(gp(crp)[h.i + 1]) - h.rs;
-    }
-  }
-  h.incl = n;
-}
-
-// Row `item` of the list (wave-uniform), or -1 past its end.
-__device__ __forceinline__ int blk_row(const int32_t *list, int item, int count) {
-  item = __builtin_amdgcn_readfirstlane(item);
-  return item < count ? __builtin_amdgcn_readfirstlane(gp(list)[item]) : -1;
-}
-
-// Entry e of the row: its part, B row and value.
-template <bool VALUES, typename VT>
-__device__ __forceinline__ void blk_entry(const BlkPart<VT> *part, int K, int e, BlkHead<VT> &h,
-                                          bool first) {
-  if (first) {
-    static_assert(SPG_MAX_PARTS <= 16, "a scan of 16 lanes");
-#pragma unroll
-    for (int off = 1; off < SPG_MAX_PARTS; off <<= 1) {
-      const int y = __shfl_up(h.incl, off);
-      if (lane_id() >= off) h.incl += y;
-    }
-    h.nA = __builtin_amdgcn_readlane(h.incl, K - 1);
-  }
-  h.k = 0;
-  int before = 0;
-  for (int k = 0; k + 1 < K; ++k) {
-    const int s = __builtin_amdgcn_readlane(h.incl, k);
-    if (e >= s) {
-      h.k = k + 1;
-      before = s;
-    }
-  }
-  const int as = K == 1 ? __builtin_amdgcn_readfirstlane(h.as) : __shfl(h.as, h.k);
-  h.r = -1;
-  if (e < h.nA) {
-    const BlkPart<VT> &P = part[h.k];
-    if (P.arp) {
-      h.r = P.acol[as + e - before];
-      if (VALUES) h.a = P.aval[as + e - before];
-    } else {
-      h.r = h.i;
-      h.a = VT(1);
-    }
-  }
-}
-
-template <typename VT>
-__device__ __forceinline__ void blk_bounds(const BlkPart<VT> *part, BlkHead<VT> &h) {
-  h.b0 = h.len = 0;
-  if (h.r >= 0) {
-    const SPG_GLOBAL int32_t *brp = part[h.k].brp;
-    h.b0 = brp[h.r];
-    h.len = brp[h.r + 1] - h.b0;
-  }
-}
 
 template <int NT, typename VT>
 struct BlkLds {
@@ -152,29 +47,8 @@ struct BlkLds {
 
 template <int NT, typename VT>
 __device__ __forceinline__ void blk_load_parts(const Problem *__restrict__ pr, BlkLds<NT, VT> &s) {
-  if (threadIdx.x < SPG_MAX_PARTS && (int)threadIdx.x < pr->K) {
-    const Part &P = pr->part[threadIdx.x];
-    s.part[threadIdx.x] = BlkPart<VT>{P.a_identity ? nullptr : gp(P.arp), gp(P.acol), gp(P.brp),
-                                      gp(P.bcol), gp(static_cast<const VT *>(P.aval)),
-                                      gp(static_cast<const VT *>(P.bval))};
-  }
-}
-
-// Block-wide exclusive scan of v (one barrier; wt is free again after the
-// caller's next one).
-template <int NT>
-__device__ __forceinline__ int blk_scan(int v, int *wt, int &total) {
-  const int x = group_incl_scan<kWave>(v), wv = threadIdx.x / kWave;
-  if (lane_id() == kWave - 1) wt[wv] = x;
-  __syncthreads();
-  int pre = 0;
-  total = 0;
-#pragma unroll
-  for (int q = 0; q < NT / kWave; ++q) {
-    pre += q < wv ? wt[q] : 0;
-    total += wt[q];
-  }
-  return pre + x - v;
+  if (threadIdx.x < SPG_MAX_PARTS && (int)threadIdx.x < pr->K)
+    s.part[threadIdx.x] = blk_part<VT>(pr->part[threadIdx.x]);
 }
 
 // The products of one chunk of at most NT entries (thread t: entry t), the
@@ -280,10 +154,6 @@ __device__ __forceinline__ int blk_chunk(BlkLds<NT, VT> &s, int K, const BlkHead
   return min(base + tot, L::CAP + 1);
 }
 
-__device__ __forceinline__ int bkt_start(const uint32_t *cnt, uint32_t b) {
-  return (int)((cnt[b >> 1] >> ((b & 1u) << 4)) & 0xffffu);
-}
-
 // Waves per SIMD the kernel is compiled for (bounds its registers): three
 // blocks of 512 threads fit a CU's LDS with FP32 values.
 template <int NT, typename VT>
@@ -357,29 +227,7 @@ __global__ __launch_bounds__(NT, (blk_waves<NT, VT>())) void k_num_block(
     __syncthreads();
     blk_parts(s.part, K, crp, nx);
     // 1. bucket starts: exclusive scan of the 16-bit counters, in place
-    {
-      const uint4 c4 = reinterpret_cast<const uint4 *>(cnt)[tid];
-      uint32_t wv[4] = {c4.x, c4.y, c4.z, c4.w};
-      int loc = 0, mx = 0;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        loc += (int)(wv[j] & 0xffffu) + (int)(wv[j] >> 16);
-        mx = max(mx, (int)max(wv[j] & 0xffffu, wv[j] >> 16));
-      }
-      mx = wave_max_last(mx);
-      if (lane_id() == kWave - 1) atomicMax(&bigmax, mx);
-      int total;
-      int run = blk_scan<NT>(loc, s.wtot, total);
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const uint32_t lo = (uint32_t)run;
-        run += (int)(wv[j] & 0xffffu);
-        const uint32_t hi = (uint32_t)run;
-        run += (int)(wv[j] >> 16);
-        wv[j] = lo | (hi << 16);
-      }
-      reinterpret_cast<uint4 *>(cnt)[tid] = make_uint4(wv[0], wv[1], wv[2], wv[3]);
-    }
+    blk_starts<NT>(cnt, &bigmax, s.wtot);
     __syncthreads();
     blk_entry<true>(s.part, K, tid, nx, true);
     const int i = h.i, rs = h.rs, nnz = h.nnz;
@@ -406,119 +254,7 @@ __global__ __launch_bounds__(NT, (blk_waves<NT, VT>())) void k_num_block(
     __syncthreads();
     blk_bounds(s.part, nx);
     h = nx;
-    const int ndup = P - nnz;  // repeated products, by the symbolic count
-    if (!big && ndup >= 0 && ndup <= kDupList) {
-      // few repeated columns.  Only products of one bucket can be out of
-      // order, so the smaller columns of a product are those placed before
-      // it, less the larger ones among its left neighbours, plus the smaller
-      // ones among its right neighbours, as far as the largest bucket
-      // reaches.  Its output rank is their number less the repeats among
-      // them, which are listed; the first product of a column sums the
-      // column's products and writes them.
-      const int *k0 = reinterpret_cast<const int *>(ikey);
-      const int reach = __builtin_amdgcn_readfirstlane(bigmax);
-      int c[kBlkE], r[kBlkE];
-      uint32_t again = 0u;  // bit j: a repeat of an earlier product's column
-#pragma unroll
-      for (int j = 0; j < kBlkE; ++j) {
-        r[j] = tid + j * NT;
-        c[j] = k0[tid + j * NT];  // past the row: unused
-      }
-      for (int d = 1; d < reach; ++d) {
-        const int *lo = k0 + (tid - d), *hi = k0 + (tid + d);
-#pragma unroll
-        for (int j = 0; j < kBlkE; ++j) {
-          if (j * NT >= P) break;
-          r[j] += hi[j * NT] < c[j] ? 1 : 0;
-          r[j] -= lo[j * NT] > c[j] ? 1 : 0;
-        }
-        if (ndup > 0) {
-#pragma unroll
-          for (int j = 0; j < kBlkE; ++j) again |= lo[j * NT] == c[j] ? 1u << j : 0u;
-        }
-      }
-      bool bad = false;
-      int nd = 0;
-      if (ndup > 0) {
-#pragma unroll
-        for (int j = 0; j < kBlkE; ++j) {
-          if (tid + j * NT < P && (again >> j & 1u)) {
-            const int e = atomicAdd(&ndl, 1);
-            if (e < kDupList) dlist[e] = (uint32_t)c[j];
-          }
-        }
-        __syncthreads();
-        nd = min(ndl, kDupList);
-        bad = ndl != ndup;  // a changed pattern
-      }
-#pragma unroll
-      for (int j = 0; j < kBlkE; ++j) {
-        const int p = tid + j * NT;
-        if (p >= P) break;
-        if (again >> j & 1u) {
-          bad = bad || ndup == 0;
-          continue;
-        }
-        VT sum = ival[p];
-        int o = r[j];
-        if (ndup > 0) {
-          for (int d = 1; d < reach && p + d < P; ++d)
-            if (k0[p + d] == c[j]) sum += ival[p + d];
-          for (int e = 0; e < nd; ++e) o -= dlist[e] < (uint32_t)c[j] ? 1 : 0;
-        }
-        if (o < nnz) {
-          cb[o] = c[j];
-          vb[o] = sum;
-        } else {
-          bad = true;
-        }
-      }
-      if (bad) atomicOr(&hdr->status, kStatInvalid);
-      continue;
-    }
-    // 3. sort every bucket of two or more products by column, or the whole
-    //    row when a bucket is large
-    if (big) lds_sort_pairs<true, NT, VT>(ikey, ival, P, tid);
-    for (int b = big ? T : tid; b < T; b += NT) {
-      const int s0 = bkt_start(cnt, (uint32_t)b);
-      const int s1 = b + 1 < T ? bkt_start(cnt, (uint32_t)b + 1) : P;
-      for (int q = s0 + 1; q < s1; ++q) {
-        const uint32_t kq = ikey[q];
-        const VT vq = ival[q];
-        int r = q - 1;
-        while (r >= s0 && ikey[r] > kq) {
-          ikey[r + 1] = ikey[r];
-          ival[r + 1] = ival[r];
-          --r;
-        }
-        ikey[r + 1] = kq;
-        ival[r + 1] = vq;
-      }
-    }
-    __syncthreads();
-    // 4. each thread a contiguous range of positions: its run starts, one
-    //    block scan, then the first of each run sums the run and writes it
-    {
-      const int per = (P + NT - 1) / NT;
-      const int p0 = tid * per, p1 = min(P, p0 + per);
-      int firsts = 0;
-      for (int p = p0; p < p1; ++p) firsts += (p == 0 || ikey[p] != ikey[p - 1]) ? 1 : 0;
-      int total;
-      int d = blk_scan<NT>(firsts, s.wtot, total);
-      for (int p = p0; p < p1; ++p) {
-        const uint32_t c = ikey[p];
-        if (p == 0 || c != ikey[p - 1]) {
-          VT sum = ival[p];
-          for (int q = p + 1; q < P && ikey[q] == c; ++q) sum += ival[q];
-          if (d < nnz) {  // the symbolic count bounds the row (a changed pattern is flagged)
-            cb[d] = (int)c;
-            vb[d] = sum;
-          }
-          ++d;
-        }
-      }
-      if (tid == 0 && total != nnz) atomicOr(&hdr->status, kStatInvalid);
-    }
+    blk_finish<NT, VT>(cnt, ikey, ival, P, nnz, big, bigmax, &ndl, dlist, s.wtot, 0, cb, vb, hdr);
   }
 }
 

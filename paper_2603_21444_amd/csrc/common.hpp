@@ -88,7 +88,7 @@ static_assert(sizeof(WsHeader) <= 256, "the operand descriptors follow at byte 2
 // Heavy rows shared by many blocks.  The symbolic pass describes each such
 // row by ranges of 2^kSplitLog2W consecutive columns (products and distinct
 // columns per range) and cuts the ranges into segments: a range with more
-// than half of kSplitSeg products stands alone, the others are grouped so
+// than a quarter of kSplitSeg products stands alone, the others are grouped so
 // that a segment holds at most kSplitSeg products.  The numeric pass first
 // scatters the row's products into per-range runs of a staging area, many
 // blocks per row (items of about kSplitItem products), then merges every
@@ -96,7 +96,9 @@ static_assert(sizeof(WsHeader) <= 256, "the operand descriptors follow at byte 2
 constexpr int kSplitLog2W = 13;         // columns per range: 8192
 constexpr int kSplitMaxRanges = 1024;   // ranges per row: n <= 2^23
 constexpr int kSplitSeg = 4096;         // products of a sorted segment at most
-constexpr int kSplitItem = 2048;        // products per scatter item (target)
+// products per scatter item (target): below the 4096 of one window of the
+// scatter, so that an item of uneven B rows rarely takes a second one
+constexpr int kSplitItem = 3584;
 
 // Counters of the split path: staging entries, segments and items reserved
 // by the symbolic pass (cleared with the header's counters), work-queue

@@ -163,10 +163,10 @@ SplitArgs split_args(const WsLayout &L, char *ws, int bin);
 SplitCtl *split_ctl(const WsLayout &L, char *ws);  // NULL when the layout has no split region
 size_t split_sym_static_lds();
 hipError_t launch_sym_split(const Problem *dpr, const int32_t *rows, WsHeader *hdr, int blo,
-                            int lS, bool lds_map, uint32_t *gbitmap, int grid, size_t lds,
+                            bool lds_map, uint32_t *gbitmap, int grid, size_t lds,
                             int32_t *cnt, const SplitArgs &sa, hipStream_t st);
 hipError_t launch_num_split(const Problem *dpr, const int32_t *rows, WsHeader *hdr, int blo,
-                            int lS, const SplitArgs &sa, int32_t *ulist, const int32_t *crp,
+                            const SplitArgs &sa, int32_t *ulist, const int32_t *crp,
                             int32_t *ccol, void *cval, bool f64, hipStream_t st);
 hipError_t configure_split_lds(size_t lds_max);
 

@@ -872,11 +872,10 @@ hipError_t launch_symbolic_bins(const Problem *dpr, const BinPlan &bp, const WsL
   const int hc = bins_count(bp, sbin, kHeavyBin);
   if (hc != 0) {
     const int grid = grid_for(hc, 1, bp.heavy_slots);
-    const int lS = sub_log2(bp, kHeavyBin, 1024);
     SplitArgs sa = split_args(L, ws, sbin);
     if (!split) sa.F = 0;
     const bool ldsmap = lds_bitmap_fits(bp.n, split_sym_static_lds());
-    return launch_sym_split(dpr, rows, hdr, sbin, lS, ldsmap,
+    return launch_sym_split(dpr, rows, hdr, sbin, ldsmap,
                             reinterpret_cast<uint32_t *>(ws + L.heavymap), grid,
                             ldsmap ? (size_t)((bp.n + 31) >> 5) * 4 : 0, cnt, sa, st);
   }
@@ -979,9 +978,8 @@ static hipError_t numeric_impl(const Problem *dpr, const BinPlan &bp, const WsLa
       const SplitArgs sa = split_args(L, ws, D.split_bin);
       // the rows left over are listed where the fallback rows were (the
       // fallback kernel above has finished with them)
-      hipError_t e = launch_num_split(dpr, rows, hdr, bp.maxbin + 1,
-                                      sub_log2(bp, kHeavyBin, kWave * 4), sa, fb, crp, ccol,
-                                      cval, sizeof(VT) == 8, st);
+      hipError_t e = launch_num_split(dpr, rows, hdr, bp.maxbin + 1, sa, fb, crp, ccol, cval,
+                                      sizeof(VT) == 8, st);
       if (e != hipSuccess) return e;
       ulist = fb;
       ucount = &sa.ctl->nuns;

@@ -13,25 +13,42 @@
 //  - the scatter kernel takes items of about kSplitItem products of any
 //    split row (a window of the row's A entries) and drops each product
 //    into its range's run of the row's staging area;
-//  - the merge kernel takes one segment at a time: at most kSplitSeg
-//    products, placed into order-preserving buckets over the segment's
-//    columns in LDS, sorted, summed by column and written at the segment's
-//    output offset; or a single range with more products, summed in a
-//    dense LDS panel of 8192 columns.
+//  - the merge kernel takes one segment at a time and writes it at its output
+//    offset: a single range of many products summed in a dense LDS panel of
+//    8192 columns; at most kSplitSeg products over a moderate span marked in
+//    a bitmap that gives every column its place; over a wider span placed
+//    into order-preserving buckets.
+//
+// What bounds them: the scatter the 8-byte staging stores (a line a lane) and
+// the gathers of B; the merge vector instructions (half its time) on segments
+// that a row's cuts leave at 1500 products of 4096; the count its two LDS
+// atomics a product and, one block a CU, the chain to a row's products.
+// R-MAT blocks, 2^20 rows, 8 parts: count 1.29 -> 0.86 ms (products spread
+// over all threads at once; the map read, counted and cleared in one sweep by
+// range; range counters in copies), scatter 1.27 -> 1.12 (one pass: a
+// product's place is its counter's old value), merge 1.41 -> 0.84.
 // A row the workspace cannot describe or stage stays with the one-block
 // heavy kernels, which take the list of such rows.
+#include <algorithm>
+
+#include "block_ops.hpp"
 #include "internal.hpp"
 #include "rowops.hpp"
 
 namespace spg {
 
 constexpr int kSplitSymUnroll = 4;
-constexpr int kSplitUnroll = 2;
-constexpr int kScatterNT = 256;         // threads of a scatter block
-constexpr int kSplitBuf = 3072;         // products an item keeps in LDS
+constexpr int kScatterNT = 512;         // threads of a scatter block
 constexpr int kAccumNT = 512;           // threads of a merge block
 constexpr int kRangeWords = (1 << kSplitLog2W) >> 5;  // bitmap words per range
-static_assert(kSplitSeg % kAccumNT == 0, "whole products per thread");
+// Segments of one range with at least this many products are summed in the
+// dense panel.
+constexpr int kDenseMin = 1024;
+// Other segments of at most this many columns find their places from a bitmap.
+// Against the buckets, R-MAT blocks of 2^20 columns: 1.17 -> 0.94 ms; with at
+// most 2^17 columns (three blocks a CU instead of two) 1.00.
+constexpr int kMapCols = 1 << 18;
+static_assert(kMapCols % (64 * kAccumNT) == 0, "whole words per thread");
 
 // ---------------------------------------------------------------------------
 // Symbolic: distinct columns of every row from bin blo on (heavy rows, one
@@ -41,15 +58,17 @@ static_assert(kSplitSeg % kAccumNT == 0, "whole products per thread");
 template <bool LDSMAP>
 __global__ __launch_bounds__(1024) void k_sym_split(const Problem *__restrict__ pr,
                                                     const int32_t *__restrict__ rows,
-                                                    WsHeader *__restrict__ hdr, int blo, int lS,
+                                                    WsHeader *__restrict__ hdr, int blo,
                                                     uint32_t *gbitmap, int32_t *cnt,
                                                     SplitArgs sa) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  __shared__ int sb[1024], sl[1024];
+  __shared__ WinLds<1024, false, float> win;
   __shared__ int pe[kSplitMaxRanges + 1], de[kSplitMaxRanges + 1];
-  __shared__ int sstart[kSplitMaxRanges];
+  // products per range in 2^plog copies, so that lanes rarely meet on one
+  // counter; later the segments' first ranges
+  __shared__ int pcnt[kSplitMaxRanges];
   __shared__ int wtot[16];
-  __shared__ int total, item, okflag, segbase, itembase, stagebase, nentries;
+  __shared__ int total, item, okflag, segbase, itembase, stagebase;
   __shared__ unsigned long long prod64;  // the row's products (the range counters are 32-bit)
   const int n = pr->n;
   const int nw = (n + 31) >> 5;
@@ -59,17 +78,17 @@ __global__ __launch_bounds__(1024) void k_sym_split(const Problem *__restrict__ 
   const int count = hdr->bin_start[kHeavyBin + 1] - start;
   const int tid = threadIdx.x;
   const int F = sa.F;
-  Stage<float> st{sb, sl, nullptr};
+  const int K = pr->K;
+  if (tid < K) win.part[tid] = blk_part<float>(pr->part[tid]);
+  const int plog = F > 0 && F <= kSplitMaxRanges / 2 ? 31 - __clz(kSplitMaxRanges / F) : 0;
+  const int pcopy = lane_id() & ((1 << plog) - 1);
+  for (int w = tid; w < nw; w += 1024) map[w] = 0u;
   for (int ri = block_next(&hdr->queue[kQueueHeavy], &item); ri < count;
        ri = block_next(&hdr->queue[kQueueHeavy], &item)) {
     const int i = rows[start + ri];
     const bool rec = F > 0 && ri < sa.hmax;  // the same in every thread
-    for (int w = tid; w < nw; w += 1024) map[w] = 0u;
-    if (rec)
-      for (int c = tid; c <= F; c += 1024) {
-        pe[c] = 0;
-        de[c] = 0;
-      }
+    static_assert(kSplitMaxRanges <= 1024, "a thread a counter");
+    if (rec && tid < kSplitMaxRanges) pcnt[tid] = 0;
     if (tid == 0) {
       total = 0;
       prod64 = 0;
@@ -77,18 +96,24 @@ __global__ __launch_bounds__(1024) void k_sym_split(const Problem *__restrict__ 
     if (!LDSMAP) __threadfence();
     __syncthreads();
     int mine = 0;  // described rows: products; others: new distinct columns
-    auto fmark = each_product([&](int col, float) {
-      const uint32_t bit = 1u << (col & 31);
-      if (rec) {  // distinct columns come from the popcounts below
-        atomicOr(&map[col >> 5], bit);
-        atomicAdd(&pe[col >> kSplitLog2W], 1);
-        ++mine;
-      } else {
-        const uint32_t old = atomicOr(&map[col >> 5], bit);
-        mine += (old & bit) ? 0 : 1;
-      }
-    });
-    for_each_product<true, false, 1024, kSplitSymUnroll, float>(pr, i, true, tid, lS, st, fmark);
+    BlkHead<float> h;
+    h.i = __builtin_amdgcn_readfirstlane(i);
+    blk_parts(win.part, K, nullptr, h);
+    blk_number(K, h);
+    blk_windows<false, kSplitSymUnroll>(
+        win, K, h, 0, h.nA, [] {},
+        [&](int, int col, float) {
+          const uint32_t bit = 1u << (col & 31);
+          if (rec) {  // distinct columns come from the popcounts below
+            atomicOr(&map[col >> 5], bit);
+            atomicAdd(&pcnt[((col >> kSplitLog2W) << plog) | pcopy], 1);
+            ++mine;
+          } else {
+            const uint32_t old = atomicOr(&map[col >> 5], bit);
+            mine += (old & bit) ? 0 : 1;
+          }
+        },
+        [] {});
     if (mine) {
       if (rec) atomicAdd(&prod64, (unsigned long long)mine);
       else atomicAdd(&total, mine);
@@ -96,19 +121,29 @@ __global__ __launch_bounds__(1024) void k_sym_split(const Problem *__restrict__ 
     if (!LDSMAP) __threadfence();
     __syncthreads();
     if (!rec) {
+      for (int w = tid; w < nw; w += 1024) map[w] = 0u;  // for the next row
       if (tid == 0) cnt[i] = total;
       continue;
     }
-    // distinct columns per range: the 64 words a wave reads lie in one range
-    for (int w0 = 0; w0 < nw; w0 += 1024) {
-      const int w = w0 + tid;
-      int pop = w < nw ? __popc(map[w]) : 0;
+    // distinct columns per range, a wave at a time; the map is clear again
+    for (int f = tid / kWave; f < F; f += 1024 / kWave) {
+      static_assert(kRangeWords == 4 * kWave, "four words a lane");
+      int pop = 0;
 #pragma unroll
-      for (int off = kWave / 2; off > 0; off >>= 1) pop += __shfl_xor(pop, off);
-      if (lane_id() == 0 && pop) atomicAdd(&de[w / kRangeWords], pop);
+      for (int q = 0; q < 4; ++q) {
+        const int w = f * kRangeWords + q * kWave + lane_id();
+        if (w < nw) {
+          pop += __popc(map[w]);
+          map[w] = 0u;
+        }
+      }
+      pop = group_incl_scan<kWave>(pop);
+      if (lane_id() == kWave - 1) de[f] = pop;
     }
     __syncthreads();
-    const int pc = tid < F ? pe[tid] : 0;
+    int pc = 0;
+    if (tid < F)
+      for (int q = 0; q < 1 << plog; ++q) pc += pcnt[(tid << plog) + q];
     const int dc = tid < F ? de[tid] : 0;
     int P, D;
     const int pex = group_excl_scan<true, 1024>(pc, tid, wtot, P);
@@ -122,10 +157,11 @@ __global__ __launch_bounds__(1024) void k_sym_split(const Problem *__restrict__ 
       de[F] = D;
     }
     __syncthreads();
-    // segment starts: a range holding more than half a segment stands
+    // segment starts: a range holding more than a quarter of a segment stands
     // alone; the others group while their product prefix stays in the same
-    // multiple of half a segment (so a group holds fewer than kSplitSeg)
-    constexpr int H = kSplitSeg / 2;
+    // multiple of three quarters (so a group holds fewer than kSplitSeg;
+    // halves instead: 10 % more time in the merge, from more segments)
+    constexpr int H = kSplitSeg * 3 / 4;
     int flag = 0;
     if (tid < F) {
       const int a = pe[tid];
@@ -133,22 +169,16 @@ __global__ __launch_bounds__(1024) void k_sym_split(const Problem *__restrict__ 
         flag = 1;
       } else {
         const int ap = pe[tid - 1];
-        const bool big = pe[tid + 1] - a > H, bigp = a - ap > H;
+        const bool big = pe[tid + 1] - a > kSplitSeg - H, bigp = a - ap > kSplitSeg - H;
         flag = (big || bigp || a / H != ap / H) ? 1 : 0;
       }
     }
+    int *sstart = pcnt;
     int nseg;
     const int sidx = group_excl_scan<true, 1024>(flag, tid, wtot, nseg);
     if (flag) sstart[sidx] = tid;
     const int J = (P + kSplitItem - 1) / kSplitItem;
     if (tid == 0) {
-      int E = 0;  // A entries of the row over all parts
-      for (int k = 0; k < pr->K; ++k) {
-        int as, ae;
-        a_row(pr->part[k], i, as, ae);
-        E += ae - as;
-      }
-      nentries = E;
       // a row of more products than the staging area holds (then its
       // 32-bit range counters may also have wrapped) is not described
       int ok = prod64 > 0 && prod64 <= (unsigned long long)sa.pcap && nseg > 0;
@@ -180,7 +210,7 @@ __global__ __launch_bounds__(1024) void k_sym_split(const Problem *__restrict__ 
             SplitSeg{ri, f0 << kSplitLog2W, min(n, f1 << kSplitLog2W), stagebase + pe[f0],
                      pe[f1] - pe[f0], de[f0], de[f1] - de[f0], -1};
       }
-      const int E = nentries;
+      const int E = h.nA;
       for (int j = tid; j < J; j += 1024)
         sa.items[itembase + j] =
             SplitItem{ri, i, (int)((int64_t)j * E / J), (int)((int64_t)(j + 1) * E / J)};
@@ -230,61 +260,6 @@ __global__ void k_split_prepare(const int32_t *__restrict__ rows, WsHeader *__re
   }
 }
 
-// Products of the item's window [e0, e1) of the row's A entries (all parts
-// in order), every lane of the block taking part.
-template <bool VALUES, typename VT, typename Fn>
-__device__ __forceinline__ void window_products(const Problem *__restrict__ pr, int i, int e0,
-                                                int e1, int tid, int lS, Stage<VT> st, Fn &f) {
-  int off = 0;
-  for (int k = 0; k < pr->K; ++k) {
-    const Part &P = pr->part[k];
-    int as, ae;
-    a_row(P, i, as, ae);
-    const int nk = ae - as;
-    const int lo = max(e0 - off, 0), hi = min(e1 - off, nk);
-    if (lo < hi)
-      part_products<true, VALUES, kScatterNT, kSplitUnroll, VT>(P, i, true, tid, lS, st, f, 0, 1,
-                                                                 lo, hi);
-    off += nk;
-  }
-}
-
-// Pass 1 of an item: products per range (LDS counters), and the products
-// themselves in the LDS buffer while it has room (slots taken per wave).
-template <typename VT>
-struct ScatterCount {
-  int *lc;
-  int *nb;
-  int32_t *bcol;
-  VT *bval;
-  template <int N>
-  __device__ __forceinline__ void batch(const int (&col)[N], const VT (&v)[N]) {
-    uint64_t m[N];
-    int tot = 0;
-#pragma unroll
-    for (int u = 0; u < N; ++u) {
-      if (col[u] >= 0) atomicAdd(&lc[col[u] >> kSplitLog2W], 1);
-      m[u] = __ballot(col[u] >= 0);
-      tot += __popcll(m[u]);
-    }
-    const uint64_t act = __ballot(true);
-    const int leader = __ffsll((unsigned long long)act) - 1;
-    int p0 = 0;
-    if (tot > 0 && lane_id() == leader) p0 = atomicAdd(nb, tot);
-    p0 = __shfl(p0, leader);
-    const uint64_t below = lanes_below();
-#pragma unroll
-    for (int u = 0; u < N; ++u) {
-      const int p = p0 + __popcll(m[u] & below);
-      p0 += __popcll(m[u]);
-      if (col[u] >= 0 && p < kSplitBuf) {
-        bcol[p] = col[u];
-        bval[p] = v[u];
-      }
-    }
-  }
-};
-
 // The staging area of the split rows: FP32 products as one 8-byte word
 // (column in the low half, value bits in the high half: one store in the
 // scatter, one load in the merge); FP64 products as a column array and a
@@ -318,39 +293,16 @@ struct Staging<float> {
   }
 };
 
-// Pass 2 of an item whose products overflowed the buffer: every product
-// straight to its range's next staging entry.
+// Numeric, step 1: items of the split rows from bin blo on, in windows of
+// eight products a thread.  A product's place among the window's products of
+// its range comes from an LDS counter; one atomic per (window, range) on the
+// row's range cursor reserves the window's run inside the range.
 template <typename VT>
-struct ScatterPlace {
-  int *lc;
-  Staging<VT> sg;
-  template <int N>
-  __device__ __forceinline__ void batch(const int (&col)[N], const VT (&v)[N]) {
-#pragma unroll
-    for (int u = 0; u < N; ++u) {
-      if (col[u] >= 0) {
-        const int p = atomicAdd(&lc[col[u] >> kSplitLog2W], 1);
-        if (p >= 0) sg.put(p, col[u], v[u]);
-      }
-    }
-  }
-};
-
-// Numeric, step 1: items of the split rows from bin blo on.  The item's
-// products are counted per range; one atomic per (item, range) on the
-// row's range cursor reserves the item's run inside the range; then each
-// product goes to the next entry of its run.
-template <typename VT>
-__global__ __launch_bounds__(kScatterNT) void k_split_scatter(const Problem *__restrict__ pr,
-                                                              WsHeader *__restrict__ hdr, int blo,
-                                                              int lS, SplitArgs sa) {
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  int32_t *bcol = reinterpret_cast<int32_t *>(smem_raw);
-  VT *bval = reinterpret_cast<VT *>(bcol + kSplitBuf);
+__global__ __launch_bounds__(kScatterNT, sizeof(VT) == 4 ? 6 : 4) void k_split_scatter(
+    const Problem *__restrict__ pr, WsHeader *__restrict__ hdr, int blo, SplitArgs sa) {
+  __shared__ WinLds<kScatterNT, true, VT> win;
   __shared__ int lc[kSplitMaxRanges];
-  __shared__ int sb[kScatterNT], sl[kScatterNT];
-  __shared__ VT sav[kScatterNT];
-  __shared__ int nb, item;
+  __shared__ int item;
   if (hdr->status) return;
   const int sbin = hdr->bin_start[sa.bin];
   const int hlo = hdr->bin_start[blo] - sbin;
@@ -358,7 +310,8 @@ __global__ __launch_bounds__(kScatterNT) void k_split_scatter(const Problem *__r
   const int tid = threadIdx.x;
   const int F = sa.F;
   const Staging<VT> stg{gpw(sa.scol), gpw(static_cast<VT *>(sa.sval))};
-  Stage<VT> st{sb, sl, sav};
+  const int K = pr->K;
+  if (tid < K) win.part[tid] = blk_part<VT>(pr->part[tid]);
   for (int t = block_next(&sa.ctl->q_scatter, &item); t < nitems;
        t = block_next(&sa.ctl->q_scatter, &item)) {
     const SplitItem it = sa.items[t];
@@ -366,41 +319,50 @@ __global__ __launch_bounds__(kScatterNT) void k_split_scatter(const Problem *__r
     if (it.h < hlo || it.h >= sa.hmax) continue;
     const int base = sa.rows[it.h].base;
     if (base < 0) continue;
-    const int i = it.i, e0 = it.e0, e1 = it.e1;
-    for (int c = tid; c < F; c += kScatterNT) lc[c] = 0;
-    if (tid == 0) nb = 0;
-    __syncthreads();
-    ScatterCount<VT> fc{lc, &nb, bcol, bval};
-    window_products<true, VT>(pr, i, e0, e1, tid, lS, st, fc);
-    __syncthreads();
-    // the item's run in each range it touches
+    BlkHead<VT> h;
+    h.i = __builtin_amdgcn_readfirstlane(it.i);
+    blk_parts(win.part, K, nullptr, h);
+    blk_number(K, h);
     const int32_t *fo = sa.fo + (size_t)it.h * (F + 1);
     int32_t *cur = sa.cur + (size_t)it.h * F;
-    for (int c = tid; c < F; c += kScatterNT) {
-      const int k = lc[c];
-      if (k) {
-        const int p = atomicAdd(&cur[c], k);
-        const int lim = fo[c + 1] - fo[c];
-        if (p > lim - k) {  // more products than the symbolic pass saw
-          atomicOr(&hdr->status, kStatInvalid);
-          lc[c] = INT32_MIN / 2;
-        } else {
-          lc[c] = base + fo[c] + p;
-        }
-      }
-    }
-    __syncthreads();
-    const int nbuf = nb;
-    if (nbuf <= kSplitBuf) {
-      for (int s = tid; s < nbuf; s += kScatterNT) {
-        const int col = bcol[s];
-        const int p = atomicAdd(&lc[col >> kSplitLog2W], 1);
-        if (p >= 0) stg.put(p, col, bval[s]);
-      }
-    } else {
-      ScatterPlace<VT> fp{lc, stg};
-      window_products<true, VT>(pr, i, e0, e1, tid, lS, st, fp);
-    }
+    int col[kBlkE], rk[kBlkE];
+    VT val[kBlkE];
+    blk_windows<true, kBlkE / 2>(
+        win, K, h, it.e0, min(it.e1, h.nA),
+        [&] {
+          for (int c = tid; c < F; c += kScatterNT) lc[c] = 0;
+#pragma unroll
+          for (int j = 0; j < kBlkE; ++j) col[j] = -1;
+        },
+        [&](int j, int c, VT v) {
+          col[j] = c;
+          val[j] = v;
+          rk[j] = atomicAdd(&lc[c >> kSplitLog2W], 1);
+        },
+        [&] {
+          __syncthreads();
+          for (int c = tid; c < F; c += kScatterNT) {
+            const int k = lc[c];
+            if (k) {
+              const int p = atomicAdd(&cur[c], k);
+              const int lim = fo[c + 1] - fo[c];
+              if (p > lim - k) {  // more products than the symbolic pass saw
+                atomicOr(&hdr->status, kStatInvalid);
+                lc[c] = -1;
+              } else {
+                lc[c] = base + fo[c] + p;
+              }
+            }
+          }
+          __syncthreads();
+#pragma unroll
+          for (int j = 0; j < kBlkE; ++j) {
+            if (col[j] >= 0) {
+              const int p = lc[col[j] >> kSplitLog2W];
+              if (p >= 0) stg.put(p + rk[j], col[j], val[j]);
+            }
+          }
+        });
   }
 }
 
@@ -410,10 +372,10 @@ __global__ __launch_bounds__(kScatterNT) void k_split_scatter(const Problem *__r
 // A single range with more products than a sorted segment holds: sums in a
 // dense LDS panel of the range's columns, a presence bitmap walked in
 // column order.  Returns the distinct columns written.
-template <typename VT>
-__device__ int merge_dense(const Staging<VT> &stg, int P,
-                           int c0, int D, VT *panel, uint32_t *bm, int *wtot,
-                           SPG_GLOBAL int32_t *cb, SPG_GLOBAL VT *vb, WsHeader *hdr) {
+template <typename VT, typename Next>
+__device__ __forceinline__ int merge_dense(const Staging<VT> &stg, int P, int c0, int D, VT *panel,
+                                           uint32_t *bm, int *wtot, SPG_GLOBAL int32_t *cb,
+                                           SPG_GLOBAL VT *vb, WsHeader *hdr, Next &next) {
   constexpr int W = 1 << kSplitLog2W;
   const int tid = threadIdx.x;
   for (int c = tid; c < W; c += kAccumNT) panel[c] = VT(0);
@@ -447,206 +409,273 @@ __device__ int merge_dense(const Staging<VT> &stg, int P,
     }
   }
   if (bad) atomicOr(&hdr->status, kStatInvalid);
+  next.ticket();
   __syncthreads();
-  uint32_t wd = tid < kRangeWords ? bm[tid] : 0u;
-  int tot;
-  int o = group_excl_scan<true, kAccumNT>(__popc(wd), tid, wtot, tot);
-  while (wd) {
-    const int c = (tid << 5) + __ffs(wd) - 1;
-    wd &= wd - 1;
-    if (o < D) {
-      cb[o] = c0 + c;
-      vb[o] = panel[c];
+  next.head();
+  // columns in order: a wave takes 1024 of them, 64 at a time
+  static_assert(kRangeWords == 32 * (kAccumNT / kWave), "32 words a wave");
+  const int lane = lane_id(), wv = tid / kWave;
+  const uint32_t mine = lane < 32 ? bm[wv * 32 + lane] : 0u;
+  const int pop = group_incl_scan<kWave>(__popc(mine));
+  if (lane == kWave - 1) wtot[wv] = pop;
+  __syncthreads();
+  next.load();
+  int o = 0, tot = 0;
+#pragma unroll
+  for (int q = 0; q < kAccumNT / kWave; ++q) {
+    o += q < wv ? wtot[q] : 0;
+    tot += wtot[q];
+  }
+#pragma unroll 4
+  for (int q = 0; q < 16; ++q) {
+    const uint64_t m = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)mine, 2 * q) |
+                       (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)mine, 2 * q + 1) << 32;
+    const int c = wv * 1024 + q * kWave + lane, p = o + mbcnt(m);
+    if ((m >> lane & 1u) && p < D) {
+      cb[p] = c0 + c;
+      vb[p] = panel[c];
     }
-    ++o;
+    o += __popcll(m);
   }
   return tot;
 }
 
-// Start of bucket b: the counters hold two 16-bit values per word.
-__device__ __forceinline__ int seg_bucket(const uint32_t *cnt, uint32_t b) {
-  return (int)((cnt[b >> 1] >> ((b & 1u) << 4)) & 0xffffu);
-}
-
-// At most kSplitSeg products over the columns [c0, c0 + span): placed into
-// T order-preserving buckets (bucket of column c: floor(c T / span), two
-// 16-bit counters per word), buckets sorted (or the whole segment when a
-// bucket is large), runs of equal columns summed.  Returns the distinct
-// columns written.
-template <typename VT>
-__device__ int merge_buckets(const Staging<VT> &stg, int P,
-                             int c0, int span, int D, uint32_t *cnt, uint32_t *ikey, VT *ival,
-                             int *wtot, int *bigmax, SPG_GLOBAL int32_t *cb, SPG_GLOBAL VT *vb,
-                             WsHeader *hdr) {
-  constexpr int J = kSplitSeg / kAccumNT;
+// At most kSplitSeg products over the columns [c0, c0 + span): a ticket in
+// the bucket floor(c T / span) of each (two 16-bit counters per word), bucket
+// starts, then the last steps of rows of one block.
+template <typename VT, typename Next>
+__device__ __forceinline__ void merge_buckets(int (&kc)[kBlkE], const VT (&kv)[kBlkE], int P,
+                                              int c0, int span, int D, uint32_t *cnt, uint32_t *ikey, VT *ival,
+                                              int *wtot, int *bigmax, int *ndl, uint32_t *dlist,
+                                              SPG_GLOBAL int32_t *cb, SPG_GLOBAL VT *vb,
+                                              WsHeader *hdr, Next &next) {
+  constexpr int J = kBlkE, T = kSplitSeg;
+  static_assert(kSplitSeg == kBlkE * kAccumNT, "eight products a thread");
   const int tid = threadIdx.x;
-  int T = 64;
-  while (T < P) T <<= 1;
-  const int TW = T >> 1;
   const uint32_t mul = T >= span ? 0xffffffffu : (uint32_t)(((uint64_t)T << 32) / (uint64_t)span);
-  for (int w = tid; w < TW; w += kAccumNT) cnt[w] = 0u;
-  if (tid == 0) *bigmax = 0;
-  __syncthreads();
-  uint32_t kc[J], kbt[J];  // column; bucket | ticket << 16 (both below 2^16)
-  VT kv[J];
-  bool bad = false;
-#pragma unroll
-  for (int j = 0; j < J; ++j) {
-    const int p = tid + j * kAccumNT;
-    kc[j] = 0u;
-    kv[j] = VT(0);
-    if (p < P) {
-      int c;
-      stg.get(p, c, kv[j]);
-      kc[j] = (uint32_t)(c - c0);
-    }
+  reinterpret_cast<uint4 *>(cnt)[tid] = make_uint4(0u, 0u, 0u, 0u);
+  if (tid == 0) {
+    *bigmax = 0;
+    *ndl = 0;
   }
+  bool bad = false;
+  __syncthreads();
 #pragma unroll
   for (int j = 0; j < J; ++j) {
     if (tid + j * kAccumNT < P) {
-      if (kc[j] >= (uint32_t)span) {  // outside the segment: a changed pattern
+      uint32_t c = (uint32_t)(kc[j] - c0);
+      if (c >= (uint32_t)span) {  // outside the segment: a changed pattern
         bad = true;
-        kc[j] = (uint32_t)span - 1;
+        c = (uint32_t)span - 1;
       }
-      const uint32_t b = mono_slot(kc[j], mul);
-      const uint32_t sh = (b & 1u) << 4;
-      kbt[j] = b | (atomicAdd(&cnt[b >> 1], 1u << sh) >> sh) << 16;
+      const uint32_t b = mono_slot(c, mul), sh = (b & 1u) << 4;
+      const uint32_t t = (atomicAdd(&cnt[b >> 1], 1u << sh) >> sh) & 0xffffu;
+      kc[j] = (int)(c | min(t, (uint32_t)kBigBucket) << 24);  // column less c0, ticket
     }
   }
   if (bad) atomicOr(&hdr->status, kStatInvalid);
+  next.ticket();
   __syncthreads();
-  // bucket starts: exclusive scan, each thread a contiguous chunk of words
-  {
-    const int per = (TW + kAccumNT - 1) / kAccumNT;
-    const int w0 = tid * per;
-    int loc = 0, mx = 0;
-    for (int q = 0; q < per; ++q)
-      if (w0 + q < TW) {
-        const uint32_t v = cnt[w0 + q];
-        loc += (int)(v & 0xffffu) + (int)(v >> 16);
-        mx = max(mx, (int)max(v & 0xffffu, v >> 16));
-      }
-    if (mx > kBigBucket) atomicMax(bigmax, mx);
-    int tot;
-    int run = group_excl_scan<true, kAccumNT>(loc, tid, wtot, tot);
-    for (int q = 0; q < per; ++q)
-      if (w0 + q < TW) {
-        const uint32_t v = cnt[w0 + q];
-        const uint32_t lo = (uint32_t)run;
-        run += (int)(v & 0xffffu);
-        cnt[w0 + q] = lo | ((uint32_t)run << 16);
-        run += (int)(v >> 16);
-      }
-  }
+  next.head();
+  blk_starts<kAccumNT>(cnt, bigmax, wtot);
   __syncthreads();
+  const int mx = *bigmax;
+  const bool big = mx > kBigBucket;
 #pragma unroll
   for (int j = 0; j < J; ++j) {
     if (tid + j * kAccumNT < P) {
-      const int pos = seg_bucket(cnt, kbt[j] & 0xffffu) + (int)(kbt[j] >> 16);
-      ikey[pos] = kc[j];
+      const uint32_t c = (uint32_t)kc[j] & 0xffffffu;
+      const int pos = big ? tid + j * kAccumNT : bkt_start(cnt, mono_slot(c, mul)) + (kc[j] >> 24);
+      ikey[pos] = c;
       ival[pos] = kv[j];
     }
   }
+  if (tid < kBigBucket) ikey[P + tid] = 0x7fffffffu;  // above every column
   __syncthreads();
-  const bool big = *bigmax > kBigBucket;
-  if (P == D && !big) {
-    // no repeated column: bucket start + smaller columns in the bucket
-    for (int p = tid; p < P; p += kAccumNT) {
-      const uint32_t c = ikey[p];
-      const uint32_t b = mono_slot(c, mul);
-      const int s0 = seg_bucket(cnt, b);
-      const int s1 = (int)b + 1 < T ? seg_bucket(cnt, b + 1) : P;
-      int r = s0;
-      for (int q = s0; q < s1; ++q) r += ikey[q] < c ? 1 : 0;
-      cb[r] = c0 + (int)c;
-      vb[r] = ival[p];
-    }
-    return P;
-  }
-  if (big) {
-    lds_sort_pairs<true, kAccumNT, VT>(ikey, ival, P, tid);
-  } else {
-    for (int b = tid; b < T; b += kAccumNT) {
-      const int s0 = seg_bucket(cnt, (uint32_t)b);
-      const int s1 = b + 1 < T ? seg_bucket(cnt, (uint32_t)b + 1) : P;
-      for (int q = s0 + 1; q < s1; ++q) {
-        const uint32_t kq = ikey[q];
-        const VT vq = ival[q];
-        int r = q - 1;
-        while (r >= s0 && ikey[r] > kq) {
-          ikey[r + 1] = ikey[r];
-          ival[r + 1] = ival[r];
-          --r;
-        }
-        ikey[r + 1] = kq;
-        ival[r + 1] = vq;
-      }
-    }
-    __syncthreads();
-  }
-  // runs of equal columns: each thread a contiguous range of positions
-  const int per = (P + kAccumNT - 1) / kAccumNT;
-  const int p0 = tid * per, p1 = min(P, p0 + per);
-  int firsts = 0;
-  for (int p = p0; p < p1; ++p) firsts += (p == 0 || ikey[p] != ikey[p - 1]) ? 1 : 0;
-  int tot;
-  int d = group_excl_scan<true, kAccumNT>(firsts, tid, wtot, tot);
-  for (int p = p0; p < p1; ++p) {
-    const uint32_t c = ikey[p];
-    if (p == 0 || c != ikey[p - 1]) {
-      VT sum = ival[p];
-      for (int q = p + 1; q < P && ikey[q] == c; ++q) sum += ival[q];
-      if (d < D) {
-        cb[d] = c0 + (int)c;
-        vb[d] = sum;
-      }
-      ++d;
-    }
-  }
-  return tot;
+  next.load();
+  blk_finish<kAccumNT, VT>(cnt, ikey, ival, P, D, big, mx, ndl, dlist, wtot, c0, cb, vb, hdr);
 }
 
+// Bitmap word w with a gap after every eight: threads that scan runs of eight
+// words do not meet on the banks.
+__device__ __forceinline__ int map_at(int w) { return w + (w >> 3); }
+constexpr int kMapWords = kMapCols / 64 + kMapCols / 512;
+
+// At most kSplitSeg products over at most kMapCols columns from c0 on: marked
+// in a bitmap, whose bits below a column are its place among the D distinct
+// ones; values summed and columns written there.
+template <typename VT, typename Next>
+__device__ __forceinline__ void merge_map(int (&kc)[kBlkE], const VT (&kv)[kBlkE], int P, int c0, int span, int D,
+                                          unsigned long long *map, uint16_t *pre, int32_t *okey,
+                                          VT *osum, int *wtot, SPG_GLOBAL int32_t *cb,
+                                          SPG_GLOBAL VT *vb, WsHeader *hdr, Next &next) {
+  constexpr int J = kBlkE;
+  const int tid = threadIdx.x;
+  const int per = (span + 64 * kAccumNT - 1) / (64 * kAccumNT);  // words a thread, 8 at most
+  for (int w = tid; w < map_at(per * kAccumNT); w += kAccumNT) map[w] = 0ull;
+  for (int d = tid; d < D; d += kAccumNT) osum[d] = VT(0);
+  __syncthreads();
+  bool bad = false;
+#pragma unroll
+  for (int j = 0; j < J; ++j) {
+    if (j * kAccumNT >= P) break;
+    uint32_t c = (uint32_t)(kc[j] - c0);
+    if (c >= (uint32_t)span) {  // outside the segment: a changed pattern
+      bad = true;
+      c = (uint32_t)span - 1;
+    }
+    kc[j] = (int)c;
+    if (tid + j * kAccumNT < P)
+      atomicOr(reinterpret_cast<uint32_t *>(map + map_at(c >> 6)) + (c >> 5 & 1u), 1u << (c & 31));
+  }
+  next.ticket();
+  __syncthreads();
+  next.head();
+  // places of the words' first columns; thread t scans words t per ...
+  int n = 0, tot;
+  for (int q = 0; q < per; ++q) n += __popcll(map[map_at(tid * per + q)]);
+  int run = blk_scan<kAccumNT>(n, wtot, tot);
+  for (int q = 0; q < per; ++q) {
+    const int w = map_at(tid * per + q);
+    pre[w] = (uint16_t)run;
+    run += __popcll(map[w]);
+  }
+  if (tid == 0) bad = bad || tot != D;
+  if (bad) atomicOr(&hdr->status, kStatInvalid);
+  __syncthreads();
+  next.load();
+#pragma unroll
+  for (int j = 0; j < J; ++j) {
+    if (j * kAccumNT >= P) break;
+    if (tid + j * kAccumNT < P) {
+      const uint32_t c = (uint32_t)kc[j];
+      const int w = map_at(c >> 6);
+      const int d = (int)pre[w] + __popcll(map[w] & ((1ull << (c & 63)) - 1ull));
+      if (d < D) {
+        okey[d] = c0 + (int)c;
+        lds_add_cas(&osum[d], kv[j]);
+      }
+    }
+  }
+  __syncthreads();
+  for (int d = tid; d < D; d += kAccumNT) {
+    if (d < tot) {
+      cb[d] = okey[d];
+      vb[d] = osum[d];
+    }
+  }
+}
+
+// What a merge block holds of its next segment: taken from the queue, read
+// and loaded while the current one is worked on.  ticket() goes before a
+// barrier, head() behind it, load() where registers allow.
 template <typename VT>
-__global__ __launch_bounds__(kAccumNT, sizeof(VT) == 4 ? 8 : 4) void k_split_merge(WsHeader *__restrict__ hdr, int blo,
+struct SegNext {
+  const SplitArgs &sa;
+  int *item;
+  int nseg, hlo, taken, t;
+  SplitSeg sg;
+  int kc[kBlkE];
+  VT kv[kBlkE];
+
+  __device__ __forceinline__ void take() {
+    if (threadIdx.x == 0) taken = atomicAdd(&sa.ctl->q_accum, 1);
+  }
+  __device__ __forceinline__ void ticket() {
+    if (threadIdx.x == 0) *item = taken;
+  }
+  __device__ __forceinline__ void head() {
+    t = __builtin_amdgcn_readfirstlane(*item);
+    if (t < nseg) sg = sa.segs[t];
+  }
+  // unused, a row of an LDS bin of this pass, or a row_ptr mismatch
+  __device__ __forceinline__ bool live() const { return t < nseg && sg.h >= hlo && sg.out >= 0; }
+  __device__ __forceinline__ bool dense() const {
+    return sg.pcount > kSplitSeg ||
+           (sg.pcount >= kDenseMin && sg.c1 - sg.c0 <= 1 << kSplitLog2W);
+  }
+  // the segment's part of the staging area (FP32: 8-byte words)
+  __device__ __forceinline__ Staging<VT> staging() const {
+    return Staging<VT>{gpw(sa.scol + (sizeof(VT) == 4 ? 2 : 1) * (size_t)sg.stage),
+                       gpw(static_cast<VT *>(sa.sval) + sg.stage)};
+  }
+  __device__ __forceinline__ void load() {
+    if (!live() || dense() || sg.pcount == 0) return;
+    const Staging<VT> stg = staging();
+#pragma unroll
+    for (int j = 0; j < kBlkE; ++j) {
+      if (j * kAccumNT >= sg.pcount) break;
+      stg.get(min((int)threadIdx.x + j * kAccumNT, sg.pcount - 1), kc[j], kv[j]);
+    }
+  }
+};
+
+template <typename VT>
+__global__ __launch_bounds__(kAccumNT, 4) void k_split_merge(WsHeader *__restrict__ hdr, int blo,
                                                           SplitArgs sa,
                                                           int32_t *__restrict__ ccol,
                                                           VT *__restrict__ cval) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  // bucket merge: counters (two per word) | keys | values; dense merge:
+  // bucket merge: values | counters (two per word) | keys; dense merge:
   // panel | bitmap
-  uint32_t *cnt = reinterpret_cast<uint32_t *>(smem_raw);
-  uint32_t *ikey = cnt + kSplitSeg / 2;
-  VT *ival = reinterpret_cast<VT *>(ikey + kSplitSeg);
+  VT *ival = reinterpret_cast<VT *>(smem_raw);
+  uint32_t *cnt = reinterpret_cast<uint32_t *>(ival + kSplitSeg);
+  uint32_t *ikey = cnt + kSplitSeg / 2 + kBigBucket;  // room for a bucket's length either side
+  unsigned long long *map = reinterpret_cast<unsigned long long *>(ival + kSplitSeg);
+  uint16_t *pre = reinterpret_cast<uint16_t *>(map + kMapWords);
+  int32_t *okey = reinterpret_cast<int32_t *>(pre + kMapWords);
   VT *panel = reinterpret_cast<VT *>(smem_raw);
   uint32_t *bm = reinterpret_cast<uint32_t *>(panel + (1 << kSplitLog2W));
   __shared__ int wtot[kAccumNT / kWave];
-  __shared__ int item, bigmax;
+  __shared__ int item, bigmax, ndl;
+  __shared__ uint32_t dlist[kDupList];
   if (hdr->status) return;
   const int sbin = hdr->bin_start[sa.bin];
   const int hlo = hdr->bin_start[blo] - sbin;
   const int nseg = min(sa.ctl->segs, sa.segcap);
   const int tid = threadIdx.x;
-  for (int t = block_next(&sa.ctl->q_accum, &item); t < nseg;
-       t = block_next(&sa.ctl->q_accum, &item)) {
-    const SplitSeg sg = sa.segs[t];
-    // unused, a row of an LDS bin of this pass, or a row_ptr mismatch
-    if (sg.h < hlo || sg.out < 0) continue;
-    if (sg.pcount == 0) {
-      if (tid == 0 && sg.dcount != 0) atomicOr(&hdr->status, kStatInvalid);
+  SegNext<VT> next{sa, &item, nseg, hlo, 0, 0, {}, {}, {}};
+  next.take();
+  next.ticket();
+  __syncthreads();
+  next.head();
+  next.load();
+  while (next.t < nseg) {
+    const SplitSeg sg = next.sg;
+    const Staging<VT> stg = next.staging();
+    const bool live = next.live(), dense = next.dense();
+    int kc[kBlkE];
+    VT kv[kBlkE];
+#pragma unroll
+    for (int j = 0; j < kBlkE; ++j) {
+      kc[j] = next.kc[j];
+      kv[j] = next.kv[j];
+    }
+    __syncthreads();  // the previous segment's last reads
+    next.take();
+    if (!live || sg.pcount == 0) {
+      if (live && tid == 0 && sg.dcount != 0) atomicOr(&hdr->status, kStatInvalid);
+      next.ticket();
+      __syncthreads();
+      next.head();
+      next.load();
       continue;
     }
-    // the segment's part of the staging area (FP32: 8-byte words)
-    const Staging<VT> stg{gpw(sa.scol + (sizeof(VT) == 4 ? 2 : 1) * (size_t)sg.stage),
-                          gpw(static_cast<VT *>(sa.sval) + sg.stage)};
     SPG_GLOBAL int32_t *cb = gpw(ccol) + sg.out;
     SPG_GLOBAL VT *vb = gpw(cval) + sg.out;
-    const int got = sg.pcount > kSplitSeg
-                        ? merge_dense<VT>(stg, sg.pcount, sg.c0, sg.dcount, panel, bm,
-                                          wtot, cb, vb, hdr)
-                        : merge_buckets<VT>(stg, sg.pcount, sg.c0, sg.c1 - sg.c0,
-                                            sg.dcount, cnt, ikey, ival, wtot, &bigmax, cb, vb,
-                                            hdr);
-    if (tid == 0 && got != sg.dcount) atomicOr(&hdr->status, kStatInvalid);
+    if (dense) {
+      const int got = merge_dense<VT>(stg, sg.pcount, sg.c0, sg.dcount, panel, bm, wtot, cb, vb,
+                                      hdr, next);
+      if (tid == 0 && got != sg.dcount) atomicOr(&hdr->status, kStatInvalid);
+    } else if (sg.c1 - sg.c0 <= kMapCols && sg.dcount <= kSplitSeg) {
+      merge_map<VT>(kc, kv, sg.pcount, sg.c0, sg.c1 - sg.c0, sg.dcount, map, pre, okey, ival, wtot,
+                    cb, vb, hdr, next);
+    } else {
+      // (the other merges use this memory too)
+      if (tid < kBigBucket) ikey[tid - kBigBucket] = 0xffffffffu;  // as an int: below every column
+      merge_buckets<VT>(kc, kv, sg.pcount, sg.c0, sg.c1 - sg.c0, sg.dcount, cnt, ikey, ival, wtot,
+                        &bigmax, &ndl, dlist, cb, vb, hdr, next);
+    }
   }
 }
 
@@ -654,20 +683,16 @@ __global__ __launch_bounds__(kAccumNT, sizeof(VT) == 4 ? 8 : 4) void k_split_mer
 // Launchers.
 
 size_t split_sym_static_lds() {
-  return (size_t)2 * 1024 * 4 + (size_t)2 * (kSplitMaxRanges + 1) * 4 +
+  return sizeof(WinLds<1024, false, float>) + (size_t)2 * (kSplitMaxRanges + 1) * 4 +
          (size_t)kSplitMaxRanges * 4 + 16 * 4 + 64;
 }
 
 template <typename VT>
-static size_t scatter_lds() {
-  return (size_t)kSplitBuf * (4 + sizeof(VT));
-}
-
-template <typename VT>
 static size_t merge_lds() {
-  const size_t buckets = (size_t)kSplitSeg * (6 + sizeof(VT));
+  const size_t buckets = (size_t)kSplitSeg * (6 + sizeof(VT)) + 2 * kBigBucket * 4;
   const size_t dense = ((size_t)sizeof(VT) << kSplitLog2W) + (size_t)kRangeWords * 4;
-  return buckets > dense ? buckets : dense;
+  const size_t map = (size_t)kSplitSeg * (4 + sizeof(VT)) + (size_t)kMapWords * 10;
+  return std::max(map, std::max(buckets, dense));
 }
 
 static int per_cu(size_t lds, size_t stat, int threads) {
@@ -679,29 +704,27 @@ static int per_cu(size_t lds, size_t stat, int threads) {
 }
 
 hipError_t launch_sym_split(const Problem *dpr, const int32_t *rows, WsHeader *hdr, int blo,
-                            int lS, bool lds_map, uint32_t *gbitmap, int grid, size_t lds,
+                            bool lds_map, uint32_t *gbitmap, int grid, size_t lds,
                             int32_t *cnt, const SplitArgs &sa, hipStream_t st) {
   if (lds_map)
     hipLaunchKernelGGL(k_sym_split<true>, dim3(grid), dim3(1024), lds, st, dpr, rows, hdr, blo,
-                       lS, (uint32_t *)nullptr, cnt, sa);
+                       (uint32_t *)nullptr, cnt, sa);
   else
     hipLaunchKernelGGL(k_sym_split<false>, dim3(grid), dim3(1024), 0, st, dpr, rows, hdr, blo,
-                       lS, gbitmap, cnt, sa);
+                       gbitmap, cnt, sa);
   return hipGetLastError();
 }
 
 template <typename VT>
-static void num_split(const Problem *dpr, const int32_t *rows, WsHeader *hdr, int blo, int lS,
+static void num_split(const Problem *dpr, const int32_t *rows, WsHeader *hdr, int blo,
                       const SplitArgs &sa, int32_t *ulist, const int32_t *crp, int32_t *ccol,
                       VT *cval, hipStream_t st) {
   const DevInfo &D = dev_info();
   hipLaunchKernelGGL(k_split_prepare, dim3(D.cus * 4), dim3(256), 0, st, rows, hdr, blo, sa,
                      crp, ulist);
-  const size_t sl = scatter_lds<VT>();
-  const int sg = D.cus * per_cu(sl, (size_t)kSplitMaxRanges * 4 + (size_t)kScatterNT * (8 + sizeof(VT)),
+  const int sg = D.cus * per_cu(0, sizeof(WinLds<kScatterNT, true, VT>) + kSplitMaxRanges * 4 + 64,
                                 kScatterNT);
-  hipLaunchKernelGGL(k_split_scatter<VT>, dim3(sg), dim3(kScatterNT), sl, st, dpr, hdr, blo, lS,
-                     sa);
+  hipLaunchKernelGGL(k_split_scatter<VT>, dim3(sg), dim3(kScatterNT), 0, st, dpr, hdr, blo, sa);
   const size_t ml = merge_lds<VT>();
   const int mg = D.cus * per_cu(ml, 256, kAccumNT);
   hipLaunchKernelGGL(k_split_merge<VT>, dim3(mg), dim3(kAccumNT), ml, st, hdr, blo, sa, ccol,
@@ -709,21 +732,19 @@ static void num_split(const Problem *dpr, const int32_t *rows, WsHeader *hdr, in
 }
 
 hipError_t launch_num_split(const Problem *dpr, const int32_t *rows, WsHeader *hdr, int blo,
-                            int lS, const SplitArgs &sa, int32_t *ulist, const int32_t *crp,
+                            const SplitArgs &sa, int32_t *ulist, const int32_t *crp,
                             int32_t *ccol, void *cval, bool f64, hipStream_t st) {
   if (sa.F <= 0) return hipSuccess;
   if (f64)
-    num_split<double>(dpr, rows, hdr, blo, lS, sa, ulist, crp, ccol, static_cast<double *>(cval), st);
+    num_split<double>(dpr, rows, hdr, blo, sa, ulist, crp, ccol, static_cast<double *>(cval), st);
   else
-    num_split<float>(dpr, rows, hdr, blo, lS, sa, ulist, crp, ccol, static_cast<float *>(cval), st);
+    num_split<float>(dpr, rows, hdr, blo, sa, ulist, crp, ccol, static_cast<float *>(cval), st);
   return hipGetLastError();
 }
 
 hipError_t configure_split_lds(size_t lds_max) {
   const void *ks[] = {
       reinterpret_cast<const void *>(&k_sym_split<true>),
-      reinterpret_cast<const void *>(&k_split_scatter<float>),
-      reinterpret_cast<const void *>(&k_split_scatter<double>),
       reinterpret_cast<const void *>(&k_split_merge<float>),
       reinterpret_cast<const void *>(&k_split_merge<double>),
   };
