@@ -24,8 +24,8 @@
 // kernels that walked the row part by part, a wave each: 8 uniform blocks,
 // 2^18 rows of 2600 products: numeric 7.20 -> 6.24 ms (4.9 without the ranks,
 // 3.9 without ranks and stores, 2.75 without the gathers either), count 3.31
-// -> 3.05; 1025..2048 products 0.67 -> 0.51 and 0.33 -> 0.22.  R-MAT blocks:
-// numeric 0.72 + 0.60 -> 0.41 + 0.45 ms, count 0.53 + 0.41 + 0.25 -> 0.20 +
+// -> 2.56; 1025..2048 products 0.67 -> 0.51 and 0.33 -> 0.22.  R-MAT blocks:
+// numeric 0.72 + 0.60 -> 0.41 + 0.45 ms, count 0.53 + 0.41 + 0.25 -> 0.18 +
 // 0.20 + 0.11 ms.
 #include <algorithm>
 
@@ -260,8 +260,14 @@ __global__ __launch_bounds__(NT, (blk_waves<NT, VT>())) void k_num_block(
 
 // a3 of the same rows: distinct columns by an LDS hash set with twice as many
 // slots as the row may have products.
+// Waves per SIMD: 512 threads spill at eight (64 registers) what six keep (80;
+// 2049..4096 products: 3.05 -> 2.56 ms, five 3.39); smaller blocks spill
+// nothing at eight (98 + 106 us against 104 + 109 at six).
 template <int NT>
-__global__ __launch_bounds__(NT, 8) void k_sym_block(const Problem *__restrict__ pr,
+constexpr int sym_blk_waves() { return NT == 512 ? 6 : 8; }
+
+template <int NT>
+__global__ __launch_bounds__(NT, (sym_blk_waves<NT>())) void k_sym_block(const Problem *__restrict__ pr,
                                                   const int32_t *__restrict__ rows,
                                                   WsHeader *__restrict__ hdr, int bin,
                                                   int32_t *__restrict__ cnt) {
@@ -387,7 +393,8 @@ static void sym_block(const Problem *dpr, const int32_t *rows, WsHeader *hdr, in
                       int32_t *cnt, hipStream_t st) {
   const DevInfo &D = dev_info();
   const size_t lds = sym_block_dyn<NT>() + sizeof(BlkLds<NT, float>) + 256;
-  int grid = D.cus * (int)std::max<size_t>(1, std::min<size_t>(D.lds_per_cu / lds, 2048 / NT));
+  int grid = D.cus * (int)std::max<size_t>(1, std::min<size_t>(D.lds_per_cu / lds,
+                                                               sym_blk_waves<NT>() * 256 / NT));
   if (count >= 0) grid = std::min(grid, count);
   hipLaunchKernelGGL((k_sym_block<NT>), dim3(grid), dim3(NT), sym_block_dyn<NT>(), st, dpr, rows,
                      hdr, b, cnt);

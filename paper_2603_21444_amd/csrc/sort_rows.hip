@@ -448,13 +448,14 @@ __global__ __launch_bounds__(256, (sort_waves<G, E>())) void k_num_sort(
 // R-MAT blocks, 2^20 rows of up to 128 products: 233 -> 181 us over the four
 // bins against the hash set; 4096 rows of 64 products 9.4 -> 4.7; 2^20 rows of
 // 16 random entries of one product each 0.32 ms either way (the gathers).
+// Up to 256 products the sort's instructions cost more than the hash set's
+// waits: 2^20 rows 0.87 ms against 0.59.
 template <int G, int E>
 __global__ __launch_bounds__(256, 8) void k_sym_sort(const Problem *__restrict__ pr,
                                                      const int32_t *__restrict__ rows,
                                                      const WsHeader *__restrict__ hdr, int bin,
                                                      int32_t *__restrict__ cnt) {
   constexpr int CAP = G * E, R = 256 / G;
-  static_assert(G < kWave, "groups inside a wave");
   __shared__ SortLds<G, E, float> lds[R];
   if (hdr->status) return;
   const int slot = threadIdx.x / G, l = threadIdx.x % G;
