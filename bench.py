@@ -444,8 +444,9 @@ def traffic_from_profile(kernel_src_hash):
 # kernels, their headers, the binning that routes its rows, the launchers);
 # the backward, MCL, permutation, split-row and one-thread-per-row sources
 # take no part in it.
-NUMERIC_SOURCES = ("api.hip", "binning.hip", "row_kernels.hip", "wave_kernels.hip",
-                   "rowops.hpp", "common.hpp", "internal.hpp")
+NUMERIC_SOURCES = ("api.hip", "binning.hip", "row_kernels.hip", "sort_rows.hip",
+                   "block_rows.hip", "block_ops.hpp", "wave_kernels.hip", "rowops.hpp",
+                   "common.hpp", "internal.hpp")
 
 
 def kernel_source_hash():
@@ -522,7 +523,7 @@ def main():
                 "rows": n, "nnz_per_row": d, "products": products, "nnz_C": r["nnz"], "seed": SEED + 1,
             },
             "roofline": {
-                "kernel": "numeric pass (row-binned LDS kernels: bucket placement, hash, sort fallback; all bins of one step)",
+                "kernel": "numeric pass (row-binned kernels: register sort, bucket placement, sort fallback; all bins of one step)",
                 "bound": "hbm",
                 "achieved": round(achieved, 2),
                 "peak": HBM_PEAK_GBS,

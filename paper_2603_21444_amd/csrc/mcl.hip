@@ -730,8 +730,9 @@ __device__ __forceinline__ int panel_accumulate(const SPG_GLOBAL int32_t *bcol,
 
 // What a panel leaves behind: every thread owns 16 of its columns (lane l of
 // wave w: 1024 w + 64 j + l, so that a wave's reads hit all banks).  Values
-// below `low` are no candidates (TRACK: absent columns have none, NaN, and
-// the largest value's smallest column is kept).
+// below `low` are no candidates (TRACK: absent columns have none, NaN).  The
+// largest value's smallest column is kept; without TRACK only one above zero,
+// which is there whatever the bitmap says.
 template <bool TRACK>
 __device__ __forceinline__ void panel_finish(unsigned long long *pacc, uint32_t *pbm, int plo,
                                              double inv_sigma, int r, bool even, float low,
@@ -740,6 +741,7 @@ __device__ __forceinline__ void panel_finish(unsigned long long *pacc, uint32_t 
   const int lane = lane_id(), c0 = threadIdx.x / kWave * (kCPT * kWave) + lane;
   ps = 0.0;
   cnt = 0;
+  uint32_t top = 0u;
   constexpr int H = kCPT / 2;
 #pragma unroll
   for (int j0 = 0; j0 < kCPT; j0 += H) {
@@ -761,11 +763,24 @@ __device__ __forceinline__ void panel_finish(unsigned long long *pacc, uint32_t 
           bcolumn = plo + c0 + jj * kWave;
         }
         if (!present) p = __uint_as_float(0x7fc00000u);
-      } else if (!even) {
-        if (acc[j] == 0ull) p = __uint_as_float(0x7fc00000u);
+      } else {
+        top = max(top, __float_as_uint(p));
+        if (!even && acc[j] == 0ull) p = __uint_as_float(0x7fc00000u);
       }
       pw[jj] = p;
       cnt += __popcll(__ballot(p >= low));
+    }
+  }
+  if (!TRACK) {  // the wave's largest value; looked up only when it grows
+    const uint32_t wtop =
+        (uint32_t)__builtin_amdgcn_readlane(wave_max_last((int)(top ^ 0x80000000u)), kWave - 1) ^
+        0x80000000u;
+    if (wtop > bbits) {
+      bbits = wtop;
+      bcolumn = INT32_MAX;  // not in this lane
+#pragma unroll
+      for (int j = kCPT - 1; j >= 0; --j)
+        if (__float_as_uint(pw[j]) == wtop) bcolumn = plo + c0 + j * kWave;
     }
   }
 }
@@ -857,8 +872,8 @@ __global__ __launch_bounds__(kPT, kPT / 256) void k_mcl_panel(
       while (lS < 6 && (double)(1 << lS) < per) ++lS;
     }
     // The bitmap is kept only where it matters: with a prune above zero a
-    // column whose sum is zero is dropped like an absent one.  A row of
-    // which nothing is left is taken once more, with it.
+    // column whose sum is zero is dropped like an absent one.  A row
+    // whose sums are all zero is taken once more, with it.
     const int mfirst = R.mn;
     double scum;
     float S;
@@ -952,12 +967,12 @@ __global__ __launch_bounds__(kPT, kPT / 256) void k_mcl_panel(
         const bool keep = idx < l1 && !(lval[idx < l1 ? idx : l0] / S < prune);
         mine += __popcll(__ballot(keep));
       }
-      R = panel_reduce(0.0, lane_id() == kWave - 1 ? mine : 0, INT32_MAX, 0ull, rs, rc, rm, rb);
+      R = panel_reduce(0.0, lane_id() == kWave - 1 ? mine : 0, INT32_MAX, bbits, rs, rc, rm, rb);
       nk = R.total;
       kept0 = __shfl(R.excl, 0);
-      if (track || (scum != 0.0 && nk > 0)) break;
-      // an emptied row, or one whose sums are all zero: its largest entry is
-      // wanted, and which columns are present matters
+      if (track || (scum != 0.0 && (nk > 0 || R.best != 0ull))) break;
+      // sums that are all zero: the largest entry is wanted, and which columns
+      // are present matters
       track = true;
       __syncthreads();
       for (int e = tid; e < nA; e += kPT) ccur[e] = gp(P.brp)[gp(P.acol)[as + e]];
@@ -1103,13 +1118,14 @@ __global__ __launch_bounds__(kPT, kPT / 256) void k_mcl_panel(
     const unsigned long long best = bcolumn < 0 ? 0ull
                                                 : ((unsigned long long)bbits << 32) |
                                                       (uint32_t)(~(uint32_t)bcolumn);
+    const int nlist = nk > 0 ? nc : 0;
     nk = 0;
-    for (int c0 = 0; c0 < nc; c0 += kPT) {
+    for (int c0 = 0; c0 < nlist; c0 += kPT) {
       const int idx = c0 + tid;
       int col = 0;
       float q = 0.f;
       bool keep = false;
-      if (idx < nc) {
+      if (idx < nlist) {
         col = lcol[idx];
         q = lval[idx] / S;
         keep = !(q < prune);
