@@ -450,6 +450,50 @@ __global__ __launch_bounds__(256) void k_scan_apply(int32_t *rp, int m, const in
   if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) rp[m] = (int32_t)hdr->nnz_total;
 }
 
+// The scan of up to 8 x 1024 counts in one block: for so few the three kernels
+// above are mostly their launches: 4096 counts 4.5 us against 10.6 (and two
+// launches), 8192 9.9 against 10.5, 16384 16.7 against 11.3.
+constexpr int kScanOne = 8;  // counts per thread
+__global__ __launch_bounds__(1024) void k_scan_one(int32_t *rp, int m, int64_t capacity,
+                                                   WsHeader *hdr) {
+  __shared__ long long wsum[1024 / kWave];
+  if (hdr->status) return;  // the counts were never written
+  const int per = (m + 1023) / 1024, i0 = threadIdx.x * per;
+  int v[kScanOne];
+  long long s = 0;
+#pragma unroll
+  for (int j = 0; j < kScanOne; ++j) {
+    v[j] = j < per && i0 + j < m ? rp[i0 + j] : 0;
+    s += v[j];
+  }
+  long long x = s;
+  for (int off = 1; off < kWave; off <<= 1) {
+    const long long y = __shfl_up(x, off);
+    if (lane_id() >= off) x += y;
+  }
+  if (lane_id() == kWave - 1) wsum[threadIdx.x / kWave] = x;
+  __syncthreads();
+  long long run = x - s, total = 0;
+  for (int w = 0; w < 1024 / kWave; ++w) {
+    if (w < (int)threadIdx.x / kWave) run += wsum[w];
+    total += wsum[w];
+  }
+  int st = 0;
+  if (total > 0x7fffffffLL) st |= kStatOverflow;
+  if (capacity >= 0 && total > capacity) st |= kStatCapacity;
+  if (threadIdx.x == 0) {
+    hdr->nnz_total = total;
+    if (st) atomicOr(&hdr->status, st);
+  }
+  if (st) return;  // row_ptr stays as it is
+#pragma unroll
+  for (int j = 0; j < kScanOne; ++j) {
+    if (j < per && i0 + j < m) rp[i0 + j] = (int32_t)run;
+    run += v[j];
+  }
+  if (threadIdx.x == 0) rp[m] = (int32_t)total;
+}
+
 // Host launchers.
 
 BinEdges default_edges() {
@@ -503,6 +547,10 @@ hipError_t launch_scan(int32_t *rp, int m, int64_t capacity, const WsLayout &L, 
   WsHeader *hdr = reinterpret_cast<WsHeader *>(ws);
   int64_t *part = reinterpret_cast<int64_t *>(ws + L.scanpart);
   const int nparts = m == 0 ? 1 : (m + kScanTile - 1) / kScanTile;
+  if (m <= kScanOne * 1024) {
+    hipLaunchKernelGGL(k_scan_one, dim3(1), dim3(1024), 0, st, rp, m, capacity, hdr);
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL(k_scan_reduce, dim3(nparts), dim3(256), 0, st, rp, m, part, hdr);
   hipLaunchKernelGGL(k_scan_mid, dim3(1), dim3(1024), 0, st, part, nparts, capacity, hdr);
   hipLaunchKernelGGL(k_scan_apply, dim3(nparts), dim3(256), 0, st, rp, m, part, hdr);

@@ -574,7 +574,7 @@ __global__ __launch_bounds__(kFewNT, 8) void k_mcl_few(
 // result is renormalised and written in column order.  (More kept entries
 // than a panel has columns, or none: the same on the list in place.)
 //
-// 2^17 rows of 400 entries (160000 products a row), per call: 136 -> 85 ms.
+// 2^17 rows of 400 entries (160000 products a row), per call: 136 -> 89 ms.
 // Of these the accumulation takes 55, bound by its reads (every panel reads
 // three lines per entry and array, 336 GB in all; generic pointers to the
 // entries' cursors made flat loads there, which waited for each other: 38 ms
