@@ -198,7 +198,7 @@ __global__ __launch_bounds__(BGeom<G>::WG) void k_bwd_rows(
     }
     group_sync<GM::BLOCK>();
     const int rs = crp[i], re = crp[i + 1];
-    for (int t = rs + l; t < re; t += G) {
+    for (uint32_t t = (uint32_t)rs + l; t < (uint32_t)re; t += G) {  // (re up to 2^31 - 1)
       const int col = ccol[t];
       uint32_t h = scramble_slot((uint32_t)col, log2T);
       int probes = 0;
@@ -360,7 +360,7 @@ __global__ __launch_bounds__(1024) void k_bwd_heavy(const Problem *__restrict__ 
        ri = block_next(&hdr->queue[kQueueHeavy], &item)) {
     const int i = rows[start + ri];
     const int rs = crp[i], re = crp[i + 1];
-    for (int t = rs + tid; t < re; t += 1024) dense[ccol[t]] = w[t];
+    for (uint32_t t = (uint32_t)rs + tid; t < (uint32_t)re; t += 1024) dense[ccol[t]] = w[t];
     __threadfence();
     __syncthreads();
     for_each_product_e<true, 1024, VT>(

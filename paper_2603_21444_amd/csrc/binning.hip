@@ -150,15 +150,17 @@ __global__ __launch_bounds__(kBinBlock) void k_rowkey(const Problem *__restrict_
         continue;
       }
       const SPG_GLOBAL int32_t *acol = gp(P.acol);
-      int p = as;
-      for (; p + 8 <= ae; p += 8) {  // eight entries, eight gathers in flight
+      // unsigned positions: a sum past a row that ends near 2^31 stays above it
+      const uint32_t pe = (uint32_t)ae;
+      uint32_t p = (uint32_t)as;
+      for (; p + 8 <= pe; p += 8) {  // eight entries, eight gathers in flight
         int r[8];
         __builtin_memcpy(&r[0], acol + p, 4 * sizeof(int));
         __builtin_memcpy(&r[4], acol + p + 4, 4 * sizeof(int));
 #pragma unroll
         for (int u = 0; u < 8; ++u) key += brow_len(brp, r[u]);
       }
-      for (; p < ae; ++p) key += brow_len(brp, acol[p]);
+      for (; p < pe; ++p) key += brow_len(brp, acol[p]);
     }
   }
   // deferred rows: long ones to the front of the list, the others to the
@@ -209,15 +211,17 @@ __device__ __forceinline__ long long row_products(const Problem *__restrict__ pr
     int as, ae;
     a_row(P, i, as, ae);
     const SPG_GLOBAL int32_t *brp = gp(P.brp);
-    int p = as + t;
-    for (; p + 3 * NT < ae; p += 4 * NT) {
+    // unsigned positions, as in k_rowkey
+    const uint32_t pe = (uint32_t)ae;
+    uint32_t p = (uint32_t)(as + t);
+    for (; p + 3 * NT < pe; p += 4 * NT) {
       int r[4];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) r[u] = a_entry_row(P, i, p + u * NT);
+      for (int u = 0; u < 4; ++u) r[u] = a_entry_row(P, i, (int)(p + u * NT));
 #pragma unroll
       for (int u = 0; u < 4; ++u) part += brow_len(brp, r[u]);
     }
-    for (; p < ae; p += NT) part += brow_len(brp, a_entry_row(P, i, p));
+    for (; p < pe; p += NT) part += brow_len(brp, a_entry_row(P, i, (int)p));
   }
   return part;
 }

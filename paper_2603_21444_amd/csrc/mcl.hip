@@ -690,9 +690,9 @@ __device__ __forceinline__ int panel_accumulate(const SPG_GLOBAL int32_t *bcol,
       float v[kPU];
 #pragma unroll
       for (int u = 0; u < kPU; ++u) {
-        const int idx = c[u] + q;
-        const bool ld = idx < en[u];
-        const uint32_t li = ld ? (uint32_t)idx : 0u;
+        const uint32_t idx = (uint32_t)(c[u] + q);  // unsigned: rows may end at 2^31 - 1
+        const bool ld = idx < (uint32_t)en[u];
+        const uint32_t li = ld ? idx : 0u;
         col[u] = bcol[li];
         v[u] = bval[li];
         col[u] = ld ? col[u] : INT32_MAX;
@@ -1234,7 +1234,8 @@ __global__ __launch_bounds__(256) void k_row_abs(const Problem *__restrict__ pr,
   for (int64_t k = wv; k < n; k += nwv) {
     const int s = gp(P.brp)[k], e = gp(P.brp)[k + 1];
     double t = 0.0;
-    for (int j = s + lane; j < e; j += kWave) t += fabs((double)bval[j]);
+    for (uint32_t j = (uint32_t)s + lane; j < (uint32_t)e; j += kWave)  // (e up to 2^31 - 1)
+      t += fabs((double)bval[j]);
 #pragma unroll
     for (int off = kWave / 2; off > 0; off >>= 1) t += __shfl_xor(t, off);
     if (lane == 0) rabs[k] = t;

@@ -1,0 +1,59 @@
+"""GPU results for operands of nearly 2^31 entries: the last rows end where a
+position plus a few lanes no longer fits 32 bits.  The other rows hold
+entries without products, so that a call costs little more than reading A."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2603_21444_amd import synth
+from helpers import assert_same_csr
+
+pytestmark = pytest.mark.gpu
+
+NNZ = 2 ** 31 - 1
+K, N = 4096, 5000     # inner dimension and columns of the result
+FIRST = 2048          # rows of B below are empty, the others hold one entry each
+
+
+def _operand(tail):
+    """Rows of 1024 entries on empty rows of B, then the rows `tail` (column
+    lists): NNZ entries in all, values 1..7 by position."""
+    import torch
+    from paper_2603_21444_amd import binding
+    t = sum(len(c) for c in tail)
+    body = NNZ - t
+    lens = np.full(-(-body // 1024), 1024, dtype=np.int64)
+    lens[0] = body - 1024 * (lens.size - 1)
+    rp = np.concatenate([[0], np.cumsum(np.concatenate([lens, [len(c) for c in tail]]))])
+    col = torch.arange(NNZ, dtype=torch.int32, device="cuda")
+    val = col.remainder(7).add_(1).float()
+    col.remainder_(1024)
+    col[body:] = torch.from_numpy(np.concatenate(tail).astype(np.int32)).cuda()
+    A = binding.DeviceCSR((rp.size - 1, K), torch.from_numpy(rp.astype(np.int32)).cuda(), col, val)
+    assert int(A.row_ptr[-1]) == NNZ
+    last = synth.HostCSR((len(tail), K), rp[-len(tail) - 1:] - body,
+                         np.concatenate(tail).astype(np.int32), val[body:].cpu().numpy())
+    return A, last
+
+
+def _one_entry_rows(first):
+    """B: rows [0, first) empty, the others with one entry each."""
+    k = np.arange(K - first)
+    ip = np.concatenate([np.zeros(first, np.int64), np.arange(K - first + 1)])
+    return synth.HostCSR((K, N), ip, (k * 37 % N).astype(np.int32),
+                         (k % 5 + 1).astype(np.float32))
+
+
+@pytest.mark.parametrize("length", [5, 250, 1024, 2000, 4000])
+def test_row_keys(length):
+    """No products at all, so only the row keys read A: rows counted by one
+    thread, by a group and by a block."""
+    from paper_2603_21444_amd import binding
+    A, _ = _operand([np.arange(length)] * 3)
+    B = binding.to_device(_one_entry_rows(K))
+    plan = binding.Plan()
+    rp, nnz = plan.symbolic([A], [B])
+    assert nnz == 0 and plan.info() == (0, 0)
+    assert int(rp.abs().max()) == 0
+    bins, _ = plan.bins()
+    assert bins[0] == A.shape[0]
