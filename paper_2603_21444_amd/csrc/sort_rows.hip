@@ -349,25 +349,29 @@ __global__ __launch_bounds__(256, (sort_waves<G, E>())) void k_num_sort(
     // further entries and parts
     for (int k = 0; k < K; ++k) {
       const Part &Pk = pr->part[k];
-      int as = 0, ae = 0;
+      // unsigned: a row may end at entry 2^31 - 1
+      uint32_t as = 0, ae = 0;
       if (k == 0) {
-        as = n0.as + G;
-        ae = n0.ae;
+        as = (uint32_t)n0.as + G;
+        ae = (uint32_t)n0.ae;
       } else if (has) {
-        a_row(Pk, i, as, ae);
+        int e0, e1;
+        a_row(Pk, i, e0, e1);
+        as = (uint32_t)e0;
+        ae = (uint32_t)e1;
       }
       while (__any(has && as < ae)) {
         int r = -1, cb = 0, cl = 0;
         VT a = VT(1);
         if (has && as + l < ae) {
-          a_entry<VT>(Pk, i, as + l, r, a);
+          a_entry<VT>(Pk, i, (int)(as + l), r, a);
           cb = gp(Pk.brp)[r];
           cl = gp(Pk.brp)[r + 1] - cb;
         }
         P = min(P, CAP + 1);
         P = sort_chunk<G, E, PAIR, true, VT>(s, gp(Pk.bcol), gp(static_cast<const VT *>(Pk.bval)),
                                        gp(Pk.pair), l, cb, cl, a, P, key);
-        as += G;
+        if (G == kWave || as < ae) as += G;
       }
     }
     n0 = n1;
@@ -495,24 +499,27 @@ __global__ __launch_bounds__(256, 8) void k_sym_sort(const Problem *__restrict__
     n2.bounds(P0, nullptr);
     for (int k = 0; k < K; ++k) {  // further entries and parts
       const Part &Pk = pr->part[k];
-      int as = 0, ae = 0;
+      uint32_t as = 0, ae = 0;
       if (k == 0) {
-        as = n0.as + G;
-        ae = n0.ae;
+        as = (uint32_t)n0.as + G;
+        ae = (uint32_t)n0.ae;
       } else if (n0.has) {
-        a_row(Pk, n0.i, as, ae);
+        int e0, e1;
+        a_row(Pk, n0.i, e0, e1);
+        as = (uint32_t)e0;
+        ae = (uint32_t)e1;
       }
       while (__any(n0.has && as < ae)) {
         int cb = 0, cl = 0;
         if (n0.has && as + l < ae) {
-          const int r = a_entry_row(Pk, n0.i, as + l);
+          const int r = a_entry_row(Pk, n0.i, (int)(as + l));
           cb = gp(Pk.brp)[r];
           cl = gp(Pk.brp)[r + 1] - cb;
         }
         P = min(P, CAP + 1);
         P = sort_chunk<G, E, false, false, float>(s, gp(Pk.bcol), none, nullptr, l, cb, cl, 1.f, P,
                                                   key);
-        as += G;
+        if (G == kWave || as < ae) as += G;
       }
     }
     group_sort<G, E>(key, l);

@@ -57,3 +57,33 @@ def test_row_keys(length):
     assert int(rp.abs().max()) == 0
     bins, _ = plan.bins()
     assert bins[0] == A.shape[0]
+
+
+def _check_tail(A, last, B, what):
+    """C = A B with eager calls: rows before the last ones empty, the last
+    ones the oracle's, exactly (small integers)."""
+    from paper_2603_21444_amd import binding
+    C = binding.spgemm(A, binding.to_device(B))
+    t = last.shape[0]
+    assert int(C.row_ptr[:-t].abs().max()) == 0
+    got = binding.DeviceCSR((t, N), C.row_ptr[-t - 1:], C.col_idx, C.vals).to_host()
+    ref, S = oracle.spgemm(last.astype(np.float64), B.astype(np.float64), with_abs=True)
+    assert_same_csr(got, ref, S, np.float32, exact=True, what=what)
+
+
+def _tail_row(products, length, rng):
+    """`length` columns of which `products` (spread evenly, the last one among
+    them) have an entry in B."""
+    c = rng.permutation(FIRST)[:length]
+    at = (np.arange(products) + 1) * length // products - 1
+    c[at] = FIRST + rng.permutation(K - FIRST)[:products]
+    return c
+
+
+@pytest.mark.parametrize("length", [17, 100, 1023])
+def test_rows_sorted_in_registers(length):
+    """Rows of 1 to 1024 products, whose A entries take one chunk or many."""
+    rng = synth.rng_for(length, 6)
+    P = [p for p in (1, 9, 16, 17, 32, 50, 64, 100, 128, 200, 256, 500, 512, 900, 1023) if p <= length]
+    A, last = _operand([_tail_row(p, length, rng) for p in P for _ in range(5)])
+    _check_tail(A, last, _one_entry_rows(FIRST), f"rows of {length}")
