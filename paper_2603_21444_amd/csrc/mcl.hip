@@ -358,11 +358,12 @@ __global__ __launch_bounds__(kFewNT, 8) void k_mcl_few(
     }
     if (it >= count) return;
     const int i = rows[start + it++];
-    int as, ae;
-    a_row(P, i, as, ae);
+    int row0, row1;
+    a_row(P, i, row0, row1);
+    const uint32_t as = (uint32_t)row0, ae = (uint32_t)row1;  // a row may end at entry 2^31 - 1
     // the scale: 2^(62 - ex) with the row's bound on sum |a b| below 2^ex
     double sb = 0.0;
-    for (int e = as + tid; e < ae; e += kFewNT)
+    for (uint32_t e = as + tid; e < ae; e += kFewNT)
       sb += fabs((double)gp(static_cast<const float *>(P.aval))[e]) * rabs[gp(P.acol)[e]];
     const double bound = group_sum<true, kFewNT>(sb, redd) * (1.0 + 1.0 / 1048576.0);
     double sigma = 1.0;
@@ -373,7 +374,7 @@ __global__ __launch_bounds__(kFewNT, 8) void k_mcl_few(
     }
     const double inv_sigma = 1.0 / sigma;  // exact: a power of two
     // 1. expansion, chunks of kFewNT entries, 8192 products at a time
-    for (int c0 = as; c0 < ae && ncols <= kFewCols; c0 += kFewNT) {
+    for (uint32_t c0 = as; c0 < ae && ncols <= kFewCols; c0 += kFewNT) {
       int b0 = 0, len = 0;
       float a = 0.f;
       if (c0 + tid < ae) {

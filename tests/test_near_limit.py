@@ -87,3 +87,52 @@ def test_rows_sorted_in_registers(length):
     P = [p for p in (1, 9, 16, 17, 32, 50, 64, 100, 128, 200, 256, 500, 512, 900, 1023) if p <= length]
     A, last = _operand([_tail_row(p, length, rng) for p in P for _ in range(5)])
     _check_tail(A, last, _one_entry_rows(FIRST), f"rows of {length}")
+
+
+def test_mcl_rows_on_few_columns():
+    """X with 2^31 - 1 entries: nearly 2^21 rows of 1024 entries whose columns
+    are empty rows of X, then rows of 257 to 1023 products on 300 columns."""
+    import torch
+    from mcl_check import check_mcl_step
+    from paper_2603_21444_amd import binding
+    n, half, ones = 1 << 22, (1 << 21) - 1000, 2048
+    rng = synth.rng_for(1, 8)
+    P = [257, 300, 512, 513, 700, 1000, 1023] * 3
+    tail = []
+    for p in P:  # p columns in [1024, 1024 + ones): rows of one entry each
+        c = np.concatenate([rng.permutation(1024)[:1023 - p], 1024 + rng.permutation(ones)[:p]])
+        tail.append(np.sort(c))
+    tail[-1] = tail[-1][1:]
+    body = NNZ - ones - sum(len(c) for c in tail)
+    lens = np.zeros(n, dtype=np.int64)
+    lens[1024:1024 + ones] = 1
+    full = body // 1024
+    lens[half:half + full] = 1024
+    lens[half + full] = body - 1024 * full
+    first = half + full + 1
+    lens[first:first + len(P)] = [len(c) for c in tail]
+    assert first + len(P) <= n - 300 and lens.sum() == NNZ
+    rp = np.concatenate([[0], np.cumsum(lens)])
+    col = torch.arange(NNZ, dtype=torch.int32, device="cuda")
+    col[ones:ones + body].sub_(ones).remainder_(1024)
+    one_col = (n - 300 + np.arange(ones) * 37 % 300).astype(np.int32)  # empty rows again
+    col[:ones] = torch.from_numpy(one_col).cuda()
+    col[ones + body:] = torch.from_numpy(np.concatenate(tail).astype(np.int32)).cuda()
+    val = torch.full((NNZ,), 1.0 / 1024, dtype=torch.float32, device="cuda")
+    w = (0.5 + rng.random(ones)).astype(np.float32)
+    val[:ones] = torch.from_numpy(w).cuda()
+    X = binding.DeviceCSR((n, n), torch.from_numpy(rp.astype(np.int32)).cuda(), col, val)
+    plan = binding.Plan()
+    got = binding.mcl_iteration(X, 2, 1e-4, 400, plan=plan, capacity=1 << 20)
+    assert plan.status() == binding.SPG_OK
+    del X, col, val
+    small = np.zeros(n, dtype=np.int64)
+    small[1024:1024 + ones] = 1
+    small[first:first + len(P)] = [len(c) for c in tail]
+    nt = sum(len(c) for c in tail)
+    Xs = synth.HostCSR((n, n), np.concatenate([[0], np.cumsum(small)]),
+                       np.concatenate([one_col, np.concatenate(tail)]).astype(np.int32),
+                       np.concatenate([w, np.full(nt, 1.0 / 1024, np.float32)]).astype(np.float32))
+    got = got.to_host()
+    assert got.indptr[first] == 0
+    assert check_mcl_step(Xs, got, 2, 1e-4, 400, rows=np.arange(first, first + len(P))) == 0
