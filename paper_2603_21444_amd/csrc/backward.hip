@@ -189,7 +189,7 @@ __global__ __launch_bounds__(BGeom<G>::WG) void k_bwd_rows(
   const int start = hdr->bin_start[bin];
   const Part &P = pr->part[0];
   const int E = det.lo ? (int)(int32_t)(uint32_t)det.mx[2] : 0;
-  for (int ri = blockIdx.x * GM::R + rslot; ri < count; ri += gridDim.x * GM::R) {
+  for (uint32_t ri = blockIdx.x * GM::R + rslot; ri < (uint32_t)count; ri += gridDim.x * GM::R) {
     int i = rows[start + ri];
     if (G >= kWave) i = __builtin_amdgcn_readfirstlane(i);
     for (int s = l; s < T; s += G) {
@@ -519,7 +519,7 @@ static hipError_t backward_impl(const Problem *dpr, const BinPlan &bp, const WsL
     const size_t lds = bwd_lds_bytes(b, G, sizeof(VT));
     int cap = D.cus * (int)std::max<size_t>(1, std::min<size_t>(D.lds_per_cu / lds, 2048 / WG));
     int grid = cap;
-    if (bp.known) grid = std::min(cap, (bp.count[b] + R - 1) / R);
+    if (bp.known) grid = (int)std::min<int64_t>(cap, ((int64_t)bp.count[b] + R - 1) / R);
     int lt = 0;
     while ((1 << lt) < bin_slots(b)) ++lt;
     int S = bp.sub[b] > 0 ? bp.sub[b] : 16;

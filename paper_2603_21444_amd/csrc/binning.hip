@@ -127,10 +127,12 @@ __global__ __launch_bounds__(kBinBlock) void k_rowkey(const Problem *__restrict_
   if (threadIdx.x < kNB) hist[threadIdx.x] = 0;
   __syncthreads();
   const int m = pr->m;
-  const int i = blockIdx.x * kBinBlock + threadIdx.x;
+  const uint32_t row = blockIdx.x * kBinBlock + threadIdx.x;  // past m: up to 2^31
+  const bool here = row < (uint32_t)m;
+  const int i = (int)row;
   int64_t key = 0;
   bool deferred = false, longrow = false;
-  if (i < m) {
+  if (here) {
     const int K = pr->K;
     int len = 0;
     for (int k = 0; k < K; ++k) {
@@ -178,9 +180,9 @@ __global__ __launch_bounds__(kBinBlock) void k_rowkey(const Problem *__restrict_
     if (deferred && longrow) longrows[lb + __popcll(lm & lt)] = i;
     if (deferred && !longrow) longrows[m - 1 - (mb + __popcll(mm & lt))] = i;
   }
-  if (i < m && deferred) {
+  if (here && deferred) {
     binid[i] = kBinDeferred;
-  } else if (i < m) {
+  } else if (here) {
     if (key == 0) cnt_zero[i] = 0;
     int b = bin_of(key, maxbin, edges);
     binid[i] = (uint8_t)b;
@@ -350,9 +352,9 @@ __global__ __launch_bounds__(kBinBlock) void k_binscatter(const uint8_t *binid, 
     if (blockIdx.x == 0) hdr->bin_start[threadIdx.x] = s;
   }
   if (hdr->status) return;
-  const int i = blockIdx.x * kBinBlock + threadIdx.x;
+  const uint32_t i = blockIdx.x * kBinBlock + threadIdx.x;  // past m: up to 2^31
   const int w = threadIdx.x / kWave;
-  const int b = i < m ? binid[i] : -1;
+  const int b = i < (uint32_t)m ? binid[i] : -1;
   int myrank = 0;
   for (int bb = 0; bb < kNB; ++bb) {
     uint64_t mask = __ballot(b == bb);
@@ -360,10 +362,10 @@ __global__ __launch_bounds__(kBinBlock) void k_binscatter(const uint8_t *binid, 
     if (lane_id() == 0) wcnt[w][bb] = __popcll(mask);
   }
   __syncthreads();
-  if (i < m) {
+  if (i < (uint32_t)m) {
     int off = binbase[b] + blockoff[(int64_t)b * gridDim.x + blockIdx.x];
     for (int ww = 0; ww < w; ++ww) off += wcnt[ww][b];
-    rows[off + myrank] = i;
+    rows[off + myrank] = (int)i;
   }
 }
 
@@ -531,7 +533,7 @@ hipError_t launch_validate(const int32_t *rp, const int32_t *col, int rows, int 
 hipError_t launch_binning(const Problem *dpr, int m, int maxbin, const BinEdges &edges,
                           const WsLayout &L, char *ws, int32_t *cnt_zero, hipStream_t st) {
   WsHeader *hdr = reinterpret_cast<WsHeader *>(ws);
-  const int nblk = m == 0 ? 1 : (m + kBinBlock - 1) / kBinBlock;
+  const int nblk = m == 0 ? 1 : (int)(((int64_t)m + kBinBlock - 1) / kBinBlock);
   uint8_t *binid = reinterpret_cast<uint8_t *>(ws + L.binid);
   int32_t *bh = reinterpret_cast<int32_t *>(ws + L.blockhist);
   int32_t *rows = reinterpret_cast<int32_t *>(ws + L.rows);
@@ -550,7 +552,7 @@ hipError_t launch_scan(int32_t *rp, int m, int64_t capacity, const WsLayout &L, 
                        hipStream_t st) {
   WsHeader *hdr = reinterpret_cast<WsHeader *>(ws);
   int64_t *part = reinterpret_cast<int64_t *>(ws + L.scanpart);
-  const int nparts = m == 0 ? 1 : (m + kScanTile - 1) / kScanTile;
+  const int nparts = m == 0 ? 1 : (int)(((int64_t)m + kScanTile - 1) / kScanTile);
   if (m <= kScanOne * 1024) {
     hipLaunchKernelGGL(k_scan_one, dim3(1), dim3(1024), 0, st, rp, m, capacity, hdr);
     return hipGetLastError();

@@ -70,7 +70,7 @@ __device__ __forceinline__ void blk_parts(const BlkPart<VT> *part, int K, const 
 // Row `item` of the list (wave-uniform), or -1 past its end.
 __device__ __forceinline__ int blk_row(const int32_t *list, int item, int count) {
   item = __builtin_amdgcn_readfirstlane(item);
-  return item < count ? __builtin_amdgcn_readfirstlane(gp(list)[item]) : -1;
+  return (uint32_t)item < (uint32_t)count ? __builtin_amdgcn_readfirstlane(gp(list)[item]) : -1;
 }
 
 // The A entries of the row numbered part by part.

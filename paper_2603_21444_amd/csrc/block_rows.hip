@@ -284,7 +284,7 @@ __global__ __launch_bounds__(NT, (sym_blk_waves<NT>())) void k_sym_block(const P
   blk_load_parts(pr, s);
   if (tid == 0) item = blockIdx.x;
   __syncthreads();
-  int it = blockIdx.x;
+  uint32_t it = blockIdx.x;
   BlkHead<float> h;
   h.i = blk_row(list, it, count);
   blk_parts(s.part, K, nullptr, h);
@@ -302,7 +302,7 @@ __global__ __launch_bounds__(NT, (sym_blk_waves<NT>())) void k_sym_block(const P
     for (int j = 0; j < kBlkE; ++j) col[j] = -1;
     it += gridDim.x;
     BlkHead<float> nx;
-    nx.i = blk_row(list, it, count);
+    nx.i = blk_row(list, (int)it, count);
     int P = blk_chunk<false, NT, float>(s, K, h, 0, col, val);
     blk_parts(s.part, K, nullptr, nx);
     for (int c0 = NT; c0 < h.nA; c0 += NT) {

@@ -97,7 +97,7 @@ __global__ __launch_bounds__(Geom<G>::WG) void k_sym_rows(const Problem *__restr
   const int count = hdr->bin_count[bin];
   const int start = hdr->bin_start[bin];
   Stage<float> st{sb, sl, nullptr};
-  for (int ri = blockIdx.x * GM::R + rslot; ri < count; ri += gridDim.x * GM::R) {
+  for (uint32_t ri = blockIdx.x * GM::R + rslot; ri < (uint32_t)count; ri += gridDim.x * GM::R) {
     const int i = uniform_if_wave<G>(rows[start + ri]);
     int4 *t4 = reinterpret_cast<int4 *>(tab);
     for (int s = l; s < T / 4; s += G) t4[s] = make_int4(kEmpty, kEmpty, kEmpty, kEmpty);
@@ -253,7 +253,7 @@ __global__ __launch_bounds__(Geom<G>::WG, num_waves<G>()) void k_num_rows(const 
   const int count = hdr->bin_count[bin];
   const int start = hdr->bin_start[bin];
   auto key_at = [&](int s) { return F32 ? slot_key(slot[s]) : key[s]; };
-  for (int ri = blockIdx.x * GM::R + rslot; ri < count; ri += gridDim.x * GM::R) {
+  for (uint32_t ri = blockIdx.x * GM::R + rslot; ri < (uint32_t)count; ri += gridDim.x * GM::R) {
     const int i = uniform_if_wave<G>(rows[start + ri]);
     if (F32) {
       int4 *s4 = reinterpret_cast<int4 *>(slot);
@@ -780,8 +780,8 @@ static int bins_count(const BinPlan &bp, int lo, int hi) {
 
 static int grid_for(int count, int rows_per_block, int cap) {
   if (count < 0) return cap;
-  const int need = (count + rows_per_block - 1) / rows_per_block;
-  return need < cap ? need : cap;
+  const int64_t need = ((int64_t)count + rows_per_block - 1) / rows_per_block;
+  return need < cap ? (int)need : cap;
 }
 
 // B-row lanes per entry, never more than the group.

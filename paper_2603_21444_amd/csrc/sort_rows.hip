@@ -270,7 +270,7 @@ struct SortNext {
   int i = 0, as = 0, ae = 0, rs = 0, re = 0;
   int r = -1;
   VT a = VT(1);
-  __device__ __forceinline__ void row(const int32_t *rows, int ri, int count) {
+  __device__ __forceinline__ void row(const int32_t *rows, uint32_t ri, uint32_t count) {
     has = ri < count;
     i = has ? group_uniform<G>(gp(rows)[ri]) : 0;
   }
@@ -309,17 +309,18 @@ __global__ __launch_bounds__(256, (sort_waves<G, E>())) void k_num_sort(
   if (hdr->status) return;
   const int slot = group_uniform<G>(threadIdx.x / G), l = threadIdx.x % G;
   SortLds<G, E, VT> &s = lds[slot];
-  const int count = hdr->bin_count[bin];
+  // unsigned: a list may hold nearly 2^31 rows
+  const uint32_t count = hdr->bin_count[bin];
   const int32_t *list = rows + hdr->bin_start[bin];
-  const int stride = gridDim.x * R;
+  const uint32_t stride = gridDim.x * R;
   const Part &P0 = pr->part[0];
   const SPG_GLOBAL int32_t *bcol0 = gp(P0.bcol);
   const SPG_GLOBAL VT *bval0 = gp(static_cast<const VT *>(P0.bval));
   const SPG_GLOBAL unsigned long long *pair0 = PAIR ? gp(P0.pair) : nullptr;
   const int K = pr->K;
-  int ri = blockIdx.x * R + slot;
+  uint32_t ri = blockIdx.x * R + slot;
   // a wave runs while any of its groups has a row
-  int wri = blockIdx.x * R + (G == kWave ? slot : (int)(threadIdx.x / kWave) * (kWave / G));
+  uint32_t wri = blockIdx.x * R + (G == kWave ? slot : (int)(threadIdx.x / kWave) * (kWave / G));
   SortNext<G, VT> n0, n1, n2;
   n0.row(list, ri, count);
   n0.bounds(P0, crp);
@@ -464,15 +465,16 @@ __global__ __launch_bounds__(256, 8) void k_sym_sort(const Problem *__restrict__
   if (hdr->status) return;
   const int slot = threadIdx.x / G, l = threadIdx.x % G;
   SortLds<G, E, float> &s = lds[slot];
-  const int count = hdr->bin_count[bin];
+  // unsigned: a list may hold nearly 2^31 rows
+  const uint32_t count = hdr->bin_count[bin];
   const int32_t *list = rows + hdr->bin_start[bin];
-  const int stride = gridDim.x * R;
+  const uint32_t stride = gridDim.x * R;
   const Part &P0 = pr->part[0];
   const SPG_GLOBAL int32_t *bcol0 = gp(P0.bcol);
   const SPG_GLOBAL float *none = nullptr;
   const int K = pr->K;
-  int ri = blockIdx.x * R + slot;
-  int wri = blockIdx.x * R + (int)(threadIdx.x / kWave) * (kWave / G);
+  uint32_t ri = blockIdx.x * R + slot;
+  uint32_t wri = blockIdx.x * R + (int)(threadIdx.x / kWave) * (kWave / G);
   SortNext<G, float> n0, n1, n2;
   n0.row(list, ri, count);
   n0.bounds(P0, nullptr);
@@ -543,7 +545,7 @@ static void sym_sort(const Problem *dpr, const int32_t *rows, const WsHeader *hd
                      int count, int32_t *cnt, hipStream_t st) {
   constexpr int R = 256 / G;
   int grid = dev_info().cus * 8;
-  if (count >= 0) grid = std::min(grid, (count + R - 1) / R);
+  if (count >= 0) grid = (int)std::min<int64_t>(grid, ((int64_t)count + R - 1) / R);
   hipLaunchKernelGGL((k_sym_sort<G, E>), dim3(std::max(1, grid)), dim3(256), 0, st, dpr, rows, hdr,
                      bin, cnt);
 }
@@ -573,7 +575,7 @@ static void num_sort(const Problem *dpr, const int32_t *rows, WsHeader *hdr, int
   const int by_waves = sort_waves<G, E>();
   const int by_lds = (int)(D.lds_per_cu / (sizeof(SortLds<G, E, VT>) * R));
   int grid = D.cus * std::max(1, std::min(by_waves, by_lds));
-  if (count >= 0) grid = std::min(grid, (count + R - 1) / R);
+  if (count >= 0) grid = (int)std::min<int64_t>(grid, ((int64_t)count + R - 1) / R);
   if constexpr (sizeof(VT) == 4) {
     if (pair) {
       hipLaunchKernelGGL((k_num_sort<G, E, true, VT>), dim3(std::max(1, grid)), dim3(256), 0, st,

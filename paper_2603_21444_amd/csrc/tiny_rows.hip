@@ -80,7 +80,7 @@ __global__ __launch_bounds__(kTinyBlock) void k_sym_tiny(const Problem *__restri
   const int count = hdr->bin_count[bin];
   const int start = hdr->bin_start[bin];
   const int t = threadIdx.x;
-  for (int ri = blockIdx.x * kTinyBlock + t; ri < count; ri += gridDim.x * kTinyBlock) {
+  for (uint32_t ri = blockIdx.x * kTinyBlock + t; ri < (uint32_t)count; ri += gridDim.x * kTinyBlock) {
     const int i = rows[start + ri];
     const int n = tiny_stage<N, false, float>(pr, i, skey, nullptr);
     uint32_t key[N];
@@ -111,7 +111,7 @@ __global__ __launch_bounds__(kTinyBlock) void k_num_tiny(const Problem *__restri
   const int count = hdr->bin_count[bin];
   const int start = hdr->bin_start[bin];
   const int t = threadIdx.x;
-  for (int ri = blockIdx.x * kTinyBlock + t; ri < count; ri += gridDim.x * kTinyBlock) {
+  for (uint32_t ri = blockIdx.x * kTinyBlock + t; ri < (uint32_t)count; ri += gridDim.x * kTinyBlock) {
     const int i = rows[start + ri];
     const int n = tiny_stage<N, true, VT>(pr, i, skey, sval);
     uint32_t key[N];

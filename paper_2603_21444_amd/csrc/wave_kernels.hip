@@ -188,7 +188,7 @@ struct NextRow {
   int as = 0, ae = 0, rs = 0, re = 0;
   int r;
   VT a;
-  __device__ __forceinline__ void link_row(const int32_t *rows, int start, int ri, int count) {
+  __device__ __forceinline__ void link_row(const int32_t *rows, int start, uint32_t ri, uint32_t count) {
     has = ri < count;
     i = has ? ufl(rows[start + ri]) : 0;
   }
@@ -278,7 +278,7 @@ __global__ __launch_bounds__(256, SPG_WAVE_WAVES) void k_sym_wave(
   const int start = hdr->bin_start[bin];
   const int stride = gridDim.x * 4;
   const Part &P0 = pr->part[0];
-  int ri = blockIdx.x * 4 + w;
+  uint32_t ri = blockIdx.x * 4 + w;
   // pipeline: n1 = next row (pointers known), n2 = row after (index known),
   // n3 = the one after that (index being fetched)
   NextRow<float> n1, n2, n3;
@@ -289,7 +289,7 @@ __global__ __launch_bounds__(256, SPG_WAVE_WAVES) void k_sym_wave(
   n1.link_row(rows, start, ri + stride, count);
   n1.link_ptrs(P0, nullptr);
   n2.link_row(rows, start, ri + 2 * stride, count);
-  for (; ri < count; ri += stride) {
+  for (; ri < (uint32_t)count; ri += stride) {
     int4 *t4 = reinterpret_cast<int4 *>(tab);
     for (int s = lane; s < T / 4; s += kWave) t4[s] = make_int4(kEmpty, kEmpty, kEmpty, kEmpty);
     group_sync<false>();
@@ -390,7 +390,7 @@ __global__ __launch_bounds__(256, SPG_WAVE_WAVES) void k_num_wave(
   const int stride = gridDim.x * 4;
   const Part &P0 = pr->part[0];
   const uint64_t below = lanes_below();
-  int ri = blockIdx.x * 4 + w;
+  uint32_t ri = blockIdx.x * 4 + w;
   NextRow<VT> n1, n2, n3;
   n1.link_row(rows, start, ri, count);
   n1.link_ptrs(P0, crp);
@@ -399,7 +399,7 @@ __global__ __launch_bounds__(256, SPG_WAVE_WAVES) void k_num_wave(
   n1.link_row(rows, start, ri + stride, count);
   n1.link_ptrs(P0, crp);
   n2.link_row(rows, start, ri + 2 * stride, count);
-  for (; ri < count; ri += stride) {
+  for (; ri < (uint32_t)count; ri += stride) {
     {
       int4 *k4 = reinterpret_cast<int4 *>(key);
       for (int s = lane; s < TT / 4; s += kWave) k4[s] = make_int4(kEmpty, kEmpty, kEmpty, kEmpty);
@@ -469,7 +469,7 @@ static int wave_grid(int count, size_t lds, int cap_waves_per_cu) {
   if (per_cu < 1) per_cu = 1;
   int grid = D.cus * per_cu;
   if (count >= 0) {
-    const int need = (count + 3) / 4;
+    const int need = (int)(((int64_t)count + 3) / 4);
     if (need < grid) grid = need;
   }
   return grid < 1 ? 1 : grid;

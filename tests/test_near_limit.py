@@ -136,3 +136,30 @@ def test_mcl_rows_on_few_columns():
     got = got.to_host()
     assert got.indptr[first] == 0
     assert check_mcl_step(Xs, got, 2, 1e-4, 400, rows=np.arange(first, first + len(P))) == 0
+
+
+@pytest.mark.parametrize("lanes", [16, 1])
+def test_as_many_rows_as_int32_counts(lanes):
+    """2^31 - 1 rows of one product each, all in one row list: the register
+    sort, and one thread per row."""
+    import torch
+    from paper_2603_21444_amd import binding
+    m = NNZ
+    rp = torch.arange(m + 1, dtype=torch.int64, device="cuda").int()
+    col = torch.arange(m, dtype=torch.int32, device="cuda").remainder_(3)
+    val = torch.arange(m, dtype=torch.int32, device="cuda").remainder_(7).float()
+    A = binding.DeviceCSR((m, 3), rp, col, val)
+    bcol, bval = (0, 5, 7), (2.0, 3.0, 5.0)
+    B = binding.to_device(synth.HostCSR((3, 8), np.arange(4), np.array(bcol, np.int32),
+                                        np.array(bval, np.float32)))
+    t = binding.default_tuning()
+    t.lanes[1] = lanes
+    plan = binding.Plan(tuning=t)
+    crp, nnz = plan.symbolic([A], [B])
+    assert nnz == m and plan.info() == (m, m) and plan.bins()[0][1] == m
+    ccol, cval = plan.numeric([A], [B], crp, nnz)
+    assert plan.status() == binding.SPG_OK
+    assert torch.equal(crp, rp)
+    for k in range(3):  # row i holds the entry of B row i mod 3
+        assert bool((ccol[k::3] == bcol[k]).all())
+        assert torch.equal(cval[k::3], val[k::3] * bval[k])
