@@ -343,7 +343,7 @@ static hipError_t permute_impl(const int32_t *arp, const int32_t *acol, const vo
                                const int32_t *lists, const WsHeader *hdr, hipStream_t st) {
   const DevInfo &D = dev_info();
   // persistent grids over the classes' lists (their lengths are on the device)
-  const int grid = std::max(1, std::min((m + 15) / 16, D.cus * 4));
+  const int grid = std::max(1, (int)std::min<int64_t>(((int64_t)m + 15) / 16, D.cus * 4));
   hipLaunchKernelGGL((k_perm_short<VT>), dim3(grid), dim3(256), 0, st, arp, acol,
                      static_cast<const VT *>(aval), prow, pcol, lists, m, brp, bcol,
                      static_cast<VT *>(bval), hdr);
@@ -374,8 +374,9 @@ hipError_t launch_permute(const spg_csr &A, const int32_t *prow, const int32_t *
   }
   // runs of whole waves, at most g blocks
   const int per = (int)((((int64_t)m + g - 1) / g + 255) / 256 * 256);
-  hipLaunchKernelGGL(k_perm_len, dim3(std::max(1, (m + per - 1) / std::max(1, per))), dim3(256), 0,
-                     st, A.row_ptr, prow, m, per, brp, longrows, hdr);
+  const int runs = m > 0 ? (int)(((int64_t)m + per - 1) / per) : 1;
+  hipLaunchKernelGGL(k_perm_len, dim3(runs), dim3(256), 0, st, A.row_ptr, prow, m, per, brp,
+                     longrows, hdr);
   WsLayout L{};
   L.scanpart = so;
   hipError_t e = launch_scan(brp, m, -1, L, ws, st);

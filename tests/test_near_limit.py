@@ -163,3 +163,31 @@ def test_as_many_rows_as_int32_counts(lanes):
     for k in range(3):  # row i holds the entry of B row i mod 3
         assert bool((ccol[k::3] == bcol[k]).all())
         assert torch.equal(cval[k::3], val[k::3] * bval[k])
+
+
+def test_permute_nearly_2_31_rows():
+    """2^31 - 1000 rows, all but the first and the last 600 empty, reversed."""
+    import torch
+    from paper_2603_21444_amd import binding
+    m, n, k = 2 ** 31 - 1000, 5000, 600
+    rng = synth.rng_for(2, 8)
+    lens = rng.integers(0, 40, size=2 * k)
+    cols = [rng.permutation(n)[:c].astype(np.int32) for c in lens]
+    small = synth.HostCSR((2 * k, n), np.concatenate([[0], np.cumsum(lens)]), np.concatenate(cols),
+                          rng.standard_normal(int(lens.sum())).astype(np.float32))
+    rp = torch.full((m + 1,), int(small.indptr[k]), dtype=torch.int32, device="cuda")
+    rp[:k + 1] = torch.from_numpy(small.indptr[:k + 1].astype(np.int32)).cuda()
+    rp[m - k:] = torch.from_numpy(small.indptr[k:].astype(np.int32)).cuda()
+    A = binding.DeviceCSR((m, n), rp, torch.from_numpy(small.indices).cuda(),
+                          torch.from_numpy(small.data).cuda())
+    q = synth.random_permutation(n, 4)
+    p = torch.arange(m, dtype=torch.int32, device="cuda").neg_().add_(m - 1)
+    plan = binding.Plan()
+    B = binding.permute(A, p, torch.from_numpy(q.astype(np.int32)).cuda(), plan=plan)
+    assert plan.status() == binding.SPG_OK
+    ref = oracle.permute(small.astype(np.float64), np.arange(2 * k)[::-1].copy(), q)
+    ip = torch.from_numpy(ref.indptr.astype(np.int32)).cuda()
+    assert torch.equal(B.row_ptr[:k + 1], ip[:k + 1]) and torch.equal(B.row_ptr[m - k:], ip[k:])
+    assert bool((B.row_ptr[k:m - k + 1] == ip[k]).all())
+    assert np.array_equal(B.col_idx.cpu().numpy(), ref.indices)
+    assert np.array_equal(B.vals.cpu().numpy().astype(np.float64), ref.data)
