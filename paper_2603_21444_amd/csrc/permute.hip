@@ -75,17 +75,29 @@ __global__ __launch_bounds__(256) void k_perm_check(const int32_t *__restrict__ 
   if (bad) atomicOr(&hdr->status, kStatInvalid);
 }
 
-// Length classes of the new rows: (0, 16], (16, 64], (64, 256] (groups of
-// 16, 16 and 64 lanes), (256, 4096] (one block per row) and longer (the
-// panel kernel); empty rows need no work.
-constexpr int kPermClasses = 5;
+// Length classes of the new rows: (0, 16], (16, 64], (64, 256], (256, 1024],
+// (1024, 4096] (groups of 16, 16, 64, 256 and 1024 lanes) and longer (in
+// panels); empty rows need no work.
+constexpr int kPermClasses = 6;
+constexpr int kPermLists = 5;  // of m places each
 
 __device__ __forceinline__ int perm_class(int len) {
-  return len <= 0 ? -1 : len <= 16 ? 0 : len <= 64 ? 1 : len <= 256 ? 2 : len <= kPermLong ? 3 : 4;
+  return len <= 0     ? -1
+         : len <= 16  ? 0
+         : len <= 64  ? 1
+         : len <= 256 ? 2
+         : len <= 1024 ? 3
+         : len <= kPermLong ? 4
+                            : 5;
 }
 
-// Length of every new row, and the old row in its class's list (class c's
-// list holds at most m rows at lists + c * m; its length is
+// Place of row `at` of class c among the lists: one list per class, the last
+// two classes share one from both ends.
+__device__ __forceinline__ int64_t perm_place(int c, int at, int m) {
+  return c < kPermLists ? (int64_t)c * m + at : (int64_t)kPermLists * m - 1 - at;
+}
+
+// Length of every new row, and the old row in its class's list (length
 // hdr->bin_count[c]).  A block takes a run of consecutive rows, so that one
 // atomic per class and block reserves its places; the rows of a list stay in
 // runs.
@@ -128,8 +140,20 @@ __global__ __launch_bounds__(256) void k_perm_len(const int32_t *__restrict__ ar
       int base = 0;
       if (lane_id() == 0) base = atomicAdd(&next[c], __popcll(mk));
       base = __shfl(base, 0);
-      if (cls == c) lists[(int64_t)c * m + base + __popcll(mk & below)] = (int)i;
+      if (cls == c) lists[perm_place(c, base + __popcll(mk & below), m)] = (int)i;
     }
+  }
+}
+
+// Adds to the ranks of a lane's first T elements the row's smaller columns.
+template <int T, int E>
+__device__ __forceinline__ void perm_ranks(const int *key_s, int len, const int (&key)[E],
+                                           int (&rank)[E]) {
+  for (int q = 0; q < len; q += 4) {  // places past the row rank last
+    const int4 k4 = *reinterpret_cast<const int4 *>(key_s + q);
+#pragma unroll
+    for (int t = 0; t < T; ++t)
+      rank[t] += (k4.x < key[t]) + (k4.y < key[t]) + (k4.z < key[t]) + (k4.w < key[t]);
   }
 }
 
@@ -217,14 +241,18 @@ __device__ __forceinline__ void perm_rows(const int32_t *__restrict__ arp,
         key_s[u * CAP + l + t * G] = key[u][t] < 0 ? INT32_MAX : key[u][t];
     group_sync<BLOCK>();
 #pragma unroll
-    for (int u = 0; u < U; ++u)
-      for (int q = 0; q < len[u]; q += 4) {  // places past the row rank last
-        const int4 k4 = *reinterpret_cast<const int4 *>(key_s + u * CAP + q);
+    for (int u = 0; u < U; ++u) {
+      // no compares for elements that no lane of the wave holds
+      int held = 1;
 #pragma unroll
-        for (int t = 0; t < E; ++t)
-          rank[u][t] += (k4.x < key[u][t]) + (k4.y < key[u][t]) + (k4.z < key[u][t]) +
-                        (k4.w < key[u][t]);
+      for (int t = 1; t < E; ++t) held += __any(key[u][t] >= 0) ? 1 : 0;
+      switch (held) {
+        case 1: perm_ranks<1, E>(key_s + u * CAP, len[u], key[u], rank[u]); break;
+        case 2: perm_ranks<E < 2 ? E : 2, E>(key_s + u * CAP, len[u], key[u], rank[u]); break;
+        case 3: perm_ranks<E < 3 ? E : 3, E>(key_s + u * CAP, len[u], key[u], rank[u]); break;
+        default: perm_ranks<E, E>(key_s + u * CAP, len[u], key[u], rank[u]);
       }
+    }
 #pragma unroll
     for (int u = 0; u < U; ++u)
 #pragma unroll
@@ -247,6 +275,7 @@ __device__ __forceinline__ void perm_rows(const int32_t *__restrict__ arp,
   }
 }
 
+// Rows of at most 1024 entries, but for those of 65..256.
 template <typename VT>
 __global__ __launch_bounds__(256) void k_perm_short(
     const int32_t *__restrict__ arp, const int32_t *__restrict__ acol,
@@ -261,17 +290,26 @@ __global__ __launch_bounds__(256) void k_perm_short(
                        skey + t / 16 * 64);
   perm_rows<16, 4, 1, VT>(arp, acol, aval, prow, pcol, lists + m, hdr->bin_count[1], brp, bcol, bval,
                        skey + t / 16 * 64);
-  perm_rows<64, 4, 1, VT>(arp, acol, aval, prow, pcol, lists + (size_t)2 * m, hdr->bin_count[2], brp,
-                       bcol, bval, skey + t / 64 * 256);
+  __syncthreads();
+  perm_rows<256, 4, 1, VT>(arp, acol, aval, prow, pcol, lists + (size_t)3 * m, hdr->bin_count[3],
+                           brp, bcol, bval, skey);
 }
 
-// One block per row: the rows of 257..kPermLong entries, then the longer
-// ones in panels of kPermPanelBits new columns; in each panel a bitmap marks the row's columns, a block scan
-// of the bitmap words gives each word's starting rank, and every element
-// writes at that rank plus the marks below it in its word (columns are
-// distinct).
+// The other rows, two blocks of 1024 threads a CU: 65..256 entries in groups
+// of 64 lanes, 1025..kPermLong one block per row, and the longest in panels of
+// kPermPanelBits new columns: a bitmap marks the row's columns, a block scan
+// of its words gives each word's starting rank, and every element writes at
+// that rank plus the marks below it in its word (columns are distinct).
+//
+// Rows of 257..1024 entries are better off in k_perm_short: their barriers
+// then hold up four waves, not sixteen (2^23 entries in rows of 300, in all:
+// 0.25 ms against 0.28).  Bound by the compares, so those of elements that a
+// wave does not hold are left out (0.25 against 0.55; rows of 1500 0.76
+// against 1.87).  One block of 1024 threads a CU for every row of more than
+// 256 entries, all compares made: rows of 300 / 700 / 1500 / 4000 took 2.07 /
+// 2.02 / 2.01 / 2.18 ms, now 0.25 / 0.43 / 0.76 / 2.02.
 template <typename VT>
-__global__ __launch_bounds__(1024) void k_perm_long(
+__global__ __launch_bounds__(1024, 8) void k_perm_long(
     const int32_t *__restrict__ arp, const int32_t *__restrict__ acol,
     const VT *__restrict__ aval, const int32_t *__restrict__ prow,
     const int32_t *__restrict__ pcol, int m, int ncols, const int32_t *__restrict__ lists,
@@ -283,13 +321,15 @@ __global__ __launch_bounds__(1024) void k_perm_long(
   __shared__ int wtot[1024 / kWave];
   __shared__ __align__(16) int skey[kPermLong];
   if (hdr->status) return;
-  perm_rows<1024, 4, 1, VT>(arp, acol, aval, prow, pcol, lists + (size_t)3 * m, hdr->bin_count[3],
-                         brp, bcol, bval, skey);
-  const int32_t *longrows = lists + (size_t)4 * m;
-  const int count = hdr->bin_count[4];
   const int tid = threadIdx.x;
+  perm_rows<64, 4, 1, VT>(arp, acol, aval, prow, pcol, lists + (size_t)2 * m, hdr->bin_count[2],
+                          brp, bcol, bval, skey + tid / 64 * 256);
+  __syncthreads();  // the groups' parts of skey change
+  perm_rows<1024, 4, 1, VT>(arp, acol, aval, prow, pcol, lists + (size_t)4 * m, hdr->bin_count[4],
+                            brp, bcol, bval, skey);
+  const int count = hdr->bin_count[5];
   for (int li = blockIdx.x; li < count; li += gridDim.x) {
-    const int i = longrows[li];
+    const int i = lists[perm_place(5, li, m)];
     const int s = arp[i], len = arp[i + 1] - s;
     int base = brp[prow ? prow[i] : i];
     for (int plo = 0; plo < ncols; plo += kPermPanelBits) {
@@ -330,7 +370,7 @@ size_t perm_workspace_bytes(int64_t m, int64_t n, size_t *rinv_off, size_t *cinv
   *cinv_off = o;
   o = al(o + 4 * (size_t)(n > 0 ? n : 1));
   *long_off = o;  // the row lists of the length classes
-  o = al(o + 4 * (size_t)kPermClasses * (size_t)(m > 0 ? m : 1));
+  o = al(o + 4 * (size_t)kPermLists * (size_t)(m > 0 ? m : 1));
   *scan_off = o;
   o = al(o + 8 * (size_t)((m + 2047) / 2048 + 1));
   return o;
@@ -343,11 +383,11 @@ static hipError_t permute_impl(const int32_t *arp, const int32_t *acol, const vo
                                const int32_t *lists, const WsHeader *hdr, hipStream_t st) {
   const DevInfo &D = dev_info();
   // persistent grids over the classes' lists (their lengths are on the device)
-  const int grid = std::max(1, (int)std::min<int64_t>(((int64_t)m + 15) / 16, D.cus * 4));
+  const int grid = std::max(1, std::min(m, D.cus * 4));
   hipLaunchKernelGGL((k_perm_short<VT>), dim3(grid), dim3(256), 0, st, arp, acol,
                      static_cast<const VT *>(aval), prow, pcol, lists, m, brp, bcol,
                      static_cast<VT *>(bval), hdr);
-  hipLaunchKernelGGL((k_perm_long<VT>), dim3(std::max(1, std::min(m, D.cus))), dim3(1024), 0, st,
+  hipLaunchKernelGGL((k_perm_long<VT>), dim3(std::max(1, std::min(m, D.cus * 2))), dim3(1024), 0, st,
                      arp, acol, static_cast<const VT *>(aval), prow, pcol, m, n, lists, brp, bcol,
                      static_cast<VT *>(bval), hdr);
   return hipGetLastError();

@@ -64,3 +64,13 @@ def test_no_permutation_after_a_good_one(where, bad):
     binding.permute(A, rows, cols, plan=plan, out=out)
     assert plan.status() == binding.SPG_ERR_INVALID
     assert all(bool((t == -7).all()) for t in out)
+
+
+@pytest.mark.parametrize("lens", [[255, 256, 257, 258], [511, 512, 513, 767, 768, 769],
+                                  [1023, 1024, 1025], [2047, 2048, 2049, 3072, 3073],
+                                  [4096, 4097, 5999, 1025, 0, 300, 4098, 2000, 64, 70] * 30,
+                                  [257, 1024, 100, 16] * 700])
+def test_rows_of_the_longer_classes(lens):
+    """Rows of 65 to 4096 entries and longer at the numbers of entries that a
+    wave or a lane starts to hold, few and more of them than blocks."""
+    test_rows_at_class_edges(lens, np.float32)
