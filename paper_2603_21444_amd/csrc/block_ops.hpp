@@ -322,11 +322,19 @@ __device__ __forceinline__ void blk_starts(uint32_t *cnt, int *bigmax, int *wt) 
   reinterpret_cast<uint4 *>(cnt)[tid] = make_uint4(wv[0], wv[1], wv[2], wv[3]);
 }
 
+// By one thread, after a barrier behind blk_finish.
+__device__ __forceinline__ void blk_unmoved(int *ndl, WsHeader *hdr) {
+  if (ndl[1] != 0) atomicOr(&hdr->status, kStatInvalid);
+  ndl[0] = ndl[1] = 0;
+}
+
 // The last steps of a row (or a segment of one, of columns from c0 on): P
 // products by bucket in ikey and ival (`big`, a bucket of more than
 // kBigBucket: in any order), mx the largest bucket, nnz distinct columns by
 // the symbolic count.  ikey has kBigBucket words below every column before it
-// and above every column behind it; *ndl is 0.
+// and above every column behind it.  ndl[0] (the repeats listed) is 0, and so
+// is ndl[1], which stays 0 unless the pattern changed: the caller looks at it
+// behind its next barrier (blk_unmoved).
 template <int NT, typename VT>
 __device__ __forceinline__ void blk_finish(uint32_t *cnt, uint32_t *ikey, VT *ival, int P, int nnz,
                                            bool big, int mx, int *ndl, uint32_t *dlist, int *wt,
@@ -342,7 +350,10 @@ __device__ __forceinline__ void blk_finish(uint32_t *cnt, uint32_t *ikey, VT *iv
     // ones among its right neighbours, as far as the largest bucket
     // reaches.  Its output rank is their number less the repeats among
     // them, which are listed; the first product of a column sums the
-    // column's products and writes them.
+    // column's products and writes them.  (A repeat's rank is not used, so
+    // an equal left neighbour may count as a larger one: every pair out of
+    // order moves one rank up and one down, and where no column repeats the
+    // moves add up to zero, which they don't in a changed pattern.)
     const int *kk = reinterpret_cast<const int *>(ikey);
     const int reach = __builtin_amdgcn_readfirstlane(mx);
     int c[kBlkE], r[kBlkE];
@@ -358,7 +369,7 @@ __device__ __forceinline__ void blk_finish(uint32_t *cnt, uint32_t *ikey, VT *iv
       for (int j = 0; j < kBlkE; ++j) {
         if (j * NT >= P) break;
         r[j] += hi[j * NT] < c[j] ? 1 : 0;
-        r[j] -= lo[j * NT] > c[j] ? 1 : 0;
+        r[j] -= lo[j * NT] >= c[j] ? 1 : 0;
       }
       if (ndup > 0) {
 #pragma unroll
@@ -366,7 +377,7 @@ __device__ __forceinline__ void blk_finish(uint32_t *cnt, uint32_t *ikey, VT *iv
       }
     }
     bool bad = false;
-    int nd = 0;
+    int nd = 0, moved = 0;
     if (ndup > 0) {
 #pragma unroll
       for (int j = 0; j < kBlkE; ++j) {
@@ -383,12 +394,10 @@ __device__ __forceinline__ void blk_finish(uint32_t *cnt, uint32_t *ikey, VT *iv
     for (int j = 0; j < kBlkE; ++j) {
       const int p = tid + j * NT;
       if (p >= P) break;
-      if (again >> j & 1u) {
-        bad = bad || ndup == 0;
-        continue;
-      }
+      if (again >> j & 1u) continue;
       VT sum = ival[p];
       int o = r[j];
+      moved += o - p;
       if (ndup > 0) {
         for (int d = 1; d < reach && p + d < P; ++d)
           if (kk[p + d] == c[j]) sum += ival[p + d];
@@ -402,6 +411,10 @@ __device__ __forceinline__ void blk_finish(uint32_t *cnt, uint32_t *ikey, VT *iv
       }
     }
     if (bad) atomicOr(&hdr->status, kStatInvalid);
+    if (ndup == 0) {
+      moved = group_incl_scan<kWave>(moved);
+      if (lane_id() == kWave - 1) atomicAdd(&ndl[1], moved);
+    }
     return;
   }
   // sort every bucket of two or more products by column, or the whole

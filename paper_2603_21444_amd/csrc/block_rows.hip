@@ -167,7 +167,7 @@ __global__ __launch_bounds__(NT, (blk_waves<NT, VT>())) void k_num_block(
   constexpr int CAP = kBlkE * NT;
   extern __shared__ __align__(16) unsigned char smem_raw[];
   __shared__ BlkLds<NT, VT> s;
-  __shared__ int bigmax, ndl, item;
+  __shared__ int bigmax, ndl[2], item;
   __shared__ uint32_t dlist[kDupList];
   const int tid = threadIdx.x;
   constexpr int T = CAP;  // buckets, two 16-bit counters per word: four words a thread
@@ -180,7 +180,10 @@ __global__ __launch_bounds__(NT, (blk_waves<NT, VT>())) void k_num_block(
   const int K = pr->K;
   if (tid < kBigBucket) ikey[tid - kBigBucket] = 0xffffffffu;  // as an int: below every column
   blk_load_parts(pr, s);
-  if (tid == 0) item = atomicAdd(&hdr->queue[bin], 1);
+  if (tid == 0) {
+    item = atomicAdd(&hdr->queue[bin], 1);
+    ndl[1] = 0;
+  }
   __syncthreads();
   BlkHead<VT> h;
   h.i = blk_row(list, item, count);
@@ -193,7 +196,7 @@ __global__ __launch_bounds__(NT, (blk_waves<NT, VT>())) void k_num_block(
     if (tid == 0) {
       item = atomicAdd(&hdr->queue[bin], 1);
       bigmax = 0;
-      ndl = 0;
+      blk_unmoved(ndl, hdr);
     }
     reinterpret_cast<uint4 *>(cnt)[tid] = make_uint4(0u, 0u, 0u, 0u);
     int col[kBlkE];
@@ -254,8 +257,10 @@ __global__ __launch_bounds__(NT, (blk_waves<NT, VT>())) void k_num_block(
     __syncthreads();
     blk_bounds(s.part, nx);
     h = nx;
-    blk_finish<NT, VT>(cnt, ikey, ival, P, nnz, big, bigmax, &ndl, dlist, s.wtot, 0, cb, vb, hdr);
+    blk_finish<NT, VT>(cnt, ikey, ival, P, nnz, big, bigmax, ndl, dlist, s.wtot, 0, cb, vb, hdr);
   }
+  __syncthreads();
+  if (tid == 0) blk_unmoved(ndl, hdr);
 }
 
 // a3 of the same rows: distinct columns by an LDS hash set with twice as many

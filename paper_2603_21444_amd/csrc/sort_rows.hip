@@ -333,6 +333,7 @@ __global__ __launch_bounds__(256, (sort_waves<G, E>())) void k_num_sort(
   n1.row(list, ri + stride, count);
   n1.bounds(P0, crp);
   n2.row(list, ri + 2 * stride, count);
+  bool again = false;
   for (; wri < count; wri += stride, ri += stride) {
     n1.entry(P0, l);
     uint32_t key[E];
@@ -386,6 +387,9 @@ __global__ __launch_bounds__(256, (sort_waves<G, E>())) void k_num_sort(
     const bool live = has && !over;
     const bool plain = live && P == nnz;
     const int p0 = l * E;
+    // the column before the lane's first one
+    const uint32_t last = G == kWave ? dpp<0x138>(key[E - 1])  // wave_shr 1
+                                     : (uint32_t)__shfl_up((int)key[E - 1], 1, G);
     if (plain) {
       int oc[E];
       VT ov[E];
@@ -394,15 +398,21 @@ __global__ __launch_bounds__(256, (sort_waves<G, E>())) void k_num_sort(
         oc[t] = (int)(key[t] >> IB);
         ov[t] = s.val[key[t] & (uint32_t)(CAP - 1)];
       }
+      // as many products as columns by the symbolic count: a column twice
+      // means a changed pattern (flagged at the end)
+      again = again || (l > 0 && p0 < P && (int)(last >> IB) == oc[0]);
       if (p0 + E <= P) {  // wide stores; the row starts anywhere (4- or 8-byte alignment)
         __builtin_memcpy(cb + p0, oc, sizeof(oc));
         __builtin_memcpy(vb + p0, ov, sizeof(ov));
+#pragma unroll
+        for (int t = 1; t < E; ++t) again = again || oc[t] == oc[t - 1];
       } else {
 #pragma unroll
         for (int t = 0; t < E; ++t) {
           if (p0 + t < P) {
             cb[p0 + t] = oc[t];
             vb[p0 + t] = ov[t];
+            again = again || (t > 0 && oc[t] == oc[t > 0 ? t - 1 : 0]);
           }
         }
       }
@@ -446,6 +456,7 @@ __global__ __launch_bounds__(256, (sort_waves<G, E>())) void k_num_sort(
     }
     group_sync<false>();
   }
+  if (again) atomicOr(&hdr->status, kStatInvalid);
 }
 
 // a3 of rows of few products: the columns sorted the same way, distinct ones

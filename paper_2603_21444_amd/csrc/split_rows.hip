@@ -454,10 +454,7 @@ __device__ __forceinline__ void merge_buckets(int (&kc)[kBlkE], const VT (&kv)[k
   const int tid = threadIdx.x;
   const uint32_t mul = T >= span ? 0xffffffffu : (uint32_t)(((uint64_t)T << 32) / (uint64_t)span);
   reinterpret_cast<uint4 *>(cnt)[tid] = make_uint4(0u, 0u, 0u, 0u);
-  if (tid == 0) {
-    *bigmax = 0;
-    *ndl = 0;
-  }
+  if (tid == 0) *bigmax = 0;
   bool bad = false;
   __syncthreads();
 #pragma unroll
@@ -627,7 +624,7 @@ __global__ __launch_bounds__(kAccumNT, 4) void k_split_merge(WsHeader *__restric
   VT *panel = reinterpret_cast<VT *>(smem_raw);
   uint32_t *bm = reinterpret_cast<uint32_t *>(panel + (1 << kSplitLog2W));
   __shared__ int wtot[kAccumNT / kWave];
-  __shared__ int item, bigmax, ndl;
+  __shared__ int item, bigmax, ndl[2];
   __shared__ uint32_t dlist[kDupList];
   if (hdr->status) return;
   const int sbin = hdr->bin_start[sa.bin];
@@ -635,6 +632,7 @@ __global__ __launch_bounds__(kAccumNT, 4) void k_split_merge(WsHeader *__restric
   const int nseg = min(sa.ctl->segs, sa.segcap);
   const int tid = threadIdx.x;
   SegNext<VT> next{sa, &item, nseg, hlo, 0, 0, {}, {}, {}};
+  if (tid == 0) ndl[0] = ndl[1] = 0;
   next.take();
   next.ticket();
   __syncthreads();
@@ -652,6 +650,7 @@ __global__ __launch_bounds__(kAccumNT, 4) void k_split_merge(WsHeader *__restric
       kv[j] = next.kv[j];
     }
     __syncthreads();  // the previous segment's last reads
+    if (tid == 0) blk_unmoved(ndl, hdr);
     next.take();
     if (!live || sg.pcount == 0) {
       if (live && tid == 0 && sg.dcount != 0) atomicOr(&hdr->status, kStatInvalid);
@@ -674,9 +673,11 @@ __global__ __launch_bounds__(kAccumNT, 4) void k_split_merge(WsHeader *__restric
       // (the other merges use this memory too)
       if (tid < kBigBucket) ikey[tid - kBigBucket] = 0xffffffffu;  // as an int: below every column
       merge_buckets<VT>(kc, kv, sg.pcount, sg.c0, sg.c1 - sg.c0, sg.dcount, cnt, ikey, ival, wtot,
-                        &bigmax, &ndl, dlist, cb, vb, hdr, next);
+                        &bigmax, ndl, dlist, cb, vb, hdr, next);
     }
   }
+  __syncthreads();
+  if (tid == 0) blk_unmoved(ndl, hdr);
 }
 
 // ---------------------------------------------------------------------------
