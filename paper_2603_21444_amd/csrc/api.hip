@@ -138,9 +138,13 @@ WsLayout ws_layout(int64_t m, int64_t n, int heavy_slots) {
   // Split heavy rows: the products are staged in the heavy accumulator
   // region (a column and an FP64 value each, whatever the pass's dtype);
   // every split row has more than 4096 products, which bounds the rows, and
-  // a row takes at most 7 segments per 3072 products (each range of more than
-  // 1024 ends one and starts the next, each multiple of 3072 starts one) and
-  // 1 item per kSplitItem, plus one.
+  // a row takes at most 1 item per kSplitItem, plus one.  The region of items
+  // and segments is as large as 3 segments and 1 item per 2048 products
+  // (changing it would change which problems fit the static scratch): after
+  // the items it has room for a segment per 630 products.  Rows give one per
+  // 1500 (R-MAT), at worst one per 440 (each range of more than 1024 ends one
+  // and starts the next, each multiple of 3072 starts one); a row that finds
+  // no room is left to the one-block kernels.
   const size_t acc_bytes = (size_t)heavy_slots * (size_t)(std::max<int64_t>(n, 1) + 4) * 8;
   const int64_t pcap = std::min<int64_t>((int64_t)(acc_bytes > 512 ? (acc_bytes - 512) / 12 : 0),
                                          (int64_t)INT32_MAX - 1);
@@ -149,7 +153,6 @@ WsLayout ws_layout(int64_t m, int64_t n, int heavy_slots) {
     L.split_F = (int)((n + (1 << kSplitLog2W) - 1) >> kSplitLog2W);
     L.split_pcap = pcap;
     L.split_hmax = (int)hmax;
-    L.split_segcap = (int)std::min<int64_t>(INT32_MAX / 2, 7 * pcap / 3072 + hmax);
     L.split_itemcap = (int)std::min<int64_t>(INT32_MAX / 2, pcap / kSplitItem + hmax);
     L.split_ctl = o;
     o = align256(o + sizeof(SplitCtl));
@@ -159,10 +162,15 @@ WsLayout ws_layout(int64_t m, int64_t n, int heavy_slots) {
     o = align256(o + (size_t)hmax * (size_t)(L.split_F + 1) * 4);
     L.split_cur = o;
     o = align256(o + (size_t)hmax * (size_t)L.split_F * 4);
-    L.split_segs = o;
-    o = align256(o + (size_t)L.split_segcap * sizeof(SplitSeg));
+    const int64_t segs = std::min<int64_t>(INT32_MAX / 2, 3 * pcap / 2048 + hmax);
+    const int64_t items = std::min<int64_t>(INT32_MAX / 2, pcap / 2048 + hmax);
+    const size_t end = align256(o + (size_t)segs * sizeof(SplitSeg)) +
+                       align256((size_t)items * sizeof(SplitItem));
     L.split_items = o;
     o = align256(o + (size_t)L.split_itemcap * sizeof(SplitItem));
+    L.split_segs = o;
+    L.split_segcap = (int)std::min<int64_t>(INT32_MAX / 2, (int64_t)((end - o) / sizeof(SplitSeg)));
+    o = end;
   }
   L.total = o;
   return L;
