@@ -287,8 +287,12 @@ int spgemm_permute(spg_plan plan, const spg_csr *A, const int32_t *row_perm,
  * columns do not fit the largest LDS table are swept in column order and
  * rely on it.  Such rows accumulate exactly-rounded products in 64-bit fixed
  * point scaled per row, so their sums do not depend on the order of the
- * adds; rows held in an LDS table (up to twice that table's product bin)
- * add in FP32, in no fixed order. */
+ * adds.  Rows held in an LDS table (up to twice that table's product bin)
+ * add products rounded to FP32: in FP32, in no fixed order, or, for rows of
+ * more than 256 products on at most 512 columns whose kept entries are all
+ * above 2^-38 of the row's sum of |products|, in 64-bit fixed point, whose
+ * error there is below that of FP32 sums.  Which of the two a row takes can
+ * differ from run to run. */
 int spgemm_mcl_workspace_size(int32_t n, int32_t topk, size_t *bytes);
 int spgemm_mcl_iteration(spg_plan plan, const spg_csr *X, int32_t r, float prune,
                          int32_t topk, int32_t *Y_row_ptr, int32_t *Y_col_idx,

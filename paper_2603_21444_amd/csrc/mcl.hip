@@ -19,6 +19,8 @@
 // and run the whole epilogue in LDS; kept entries are flagged by clearing
 // the sign of their value slot.  Rows beyond the tables are swept in column
 // panels (k_mcl_panel below).
+#include <float.h>
+
 #include <vector>
 
 #include "internal.hpp"
@@ -290,7 +292,10 @@ __global__ __launch_bounds__(MGeom<G>::WG) void k_mcl_rows(
 // do not depend on the order of the adds), products numbered over the row's
 // entries as in k_num_sort, so that every thread has four of them in flight.
 // A row with more columns is given back to k_mcl_rows (its length is set to
-// kMclPending); when a quarter of the rows taken so far were given back, the
+// kMclPending), and so is one that FP32 sums serve better: an entry's error is
+// half a unit (2^-61 of the row's bound at most) per product, so a kept entry
+// of less than 2^24 units could lose more than FP32 sums do; and rows whose
+// sum is zero or whose products may not be finite.  When a quarter of the rows taken so far were given back, the
 // rest of the bin is left to that kernel.
 //
 // k_mcl_rows sizes its table by the products, holds one row per CU, and its
@@ -366,13 +371,20 @@ __global__ __launch_bounds__(kFewNT, 8) void k_mcl_few(
     for (uint32_t e = as + tid; e < ae; e += kFewNT)
       sb += fabs((double)gp(static_cast<const float *>(P.aval))[e]) * rabs[gp(P.acol)[e]];
     const double bound = group_sum<true, kFewNT>(sb, redd) * (1.0 + 1.0 / 1048576.0);
-    double sigma = 1.0;
-    if (bound > 0.0 && bound < 1e300) {
-      int ex = 0;
-      (void)frexp(bound, &ex);
-      sigma = ldexp(1.0, 62 - (ex < -960 ? -960 : ex));
-    }
+    int ex = 0;
+    (void)frexp(bound, &ex);
+    const double sigma = ldexp(1.0, 62 - ex);
     const double inv_sigma = 1.0 / sigma;  // exact: a power of two
+    auto give_back = [&] {
+      if (tid == 0) {
+        ycnt[i] = kMclPending;
+        atomicAdd(&failed[bin], 1);
+      }
+    };
+    if (!(bound > 0.0 && bound < (double)FLT_MAX)) {  // no product overflows below
+      give_back();
+      continue;
+    }
     // 1. expansion, chunks of kFewNT entries, 8192 products at a time
     for (uint32_t c0 = as; c0 < ae && ncols <= kFewCols; c0 += kFewNT) {
       int b0 = 0, len = 0;
@@ -442,10 +454,7 @@ __global__ __launch_bounds__(kFewNT, 8) void k_mcl_few(
     }
     __syncthreads();
     if (ncols > kFewCols) {
-      if (tid == 0) {
-        ycnt[i] = kMclPending;
-        atomicAdd(&failed[bin], 1);
-      }
+      give_back();
       continue;
     }
     // 2.-4. inflation, row sum, prune (thread t: slots t + 256 j)
@@ -453,10 +462,12 @@ __global__ __launch_bounds__(kFewNT, 8) void k_mcl_few(
     int sc[J];
     float sv[J];
     double part = 0.0;
+    bool weak[J];
 #pragma unroll
     for (int j = 0; j < J; ++j) {
       const int s = tid + j * kFewNT;
       sc[j] = key[s];
+      weak[j] = acc[s] + (1ull << 24) < (2ull << 24);  // fewer than 2^24 units either way
       sv[j] = ipow((float)((double)(long long)acc[s] * inv_sigma), r);
       part += sc[j] != kEmpty ? (double)sv[j] : 0.0;
     }
@@ -470,9 +481,13 @@ __global__ __launch_bounds__(kFewNT, 8) void k_mcl_few(
       sv[j] = sv[j] / S;
       keep[j] = sc[j] != kEmpty && !(sv[j] < prune);
       if (sc[j] != kEmpty && kk > best) best = kk;
-      kept += keep[j] ? 1 : 0;
+      kept += keep[j] ? 1 + (weak[j] ? 1 << 16 : 0) : 0;  // weak ones in the upper half
     }
     const int nkept = group_sum<true, kFewNT>(kept, redi);
+    if (nkept >> 16 || !(S > 0.f && S <= FLT_MAX)) {
+      give_back();
+      continue;
+    }
     if (nkept > topk) {
       // 5. the largest bit pattern tau with at least topk kept values >= tau;
       //    ties at tau: the smallest columns
@@ -513,6 +528,13 @@ __global__ __launch_bounds__(kFewNT, 8) void k_mcl_few(
       const int bcolm = (int)~(uint32_t)(bb & 0xffffffffu);
 #pragma unroll
       for (int j = 0; j < J; ++j) keep[j] = sc[j] != kEmpty && sc[j] == bcolm;
+      bool w = false;
+#pragma unroll
+      for (int j = 0; j < J; ++j) w = w || (keep[j] && weak[j]);
+      if (__syncthreads_or(w)) {
+        give_back();
+        continue;
+      }
     }
     // 7. the kept columns' new sum and order: rank = kept columns below
     double part2 = 0.0;

@@ -74,3 +74,40 @@ def test_many_rows_given_back():
     hundreds the rest of the bin is left to the hash kernel."""
     X = _clusters([25] * 200, 9, spread=4000)
     check_mcl_step(X, _run(X, r=2, prune=1e-6, topk=4000), 2, 1e-6, 4000, rows=np.arange(0, 5000, 3))
+
+
+def _scaled_columns(decades, seed):
+    """Clusters of 40 and 90 vertices whose columns differ in size by up to
+    10^decades, the same in all rows."""
+    X = _clusters([40] * 20 + [90] * 8, seed)
+    scale = 10.0 ** -(decades * synth.rng_for(seed, 5).random(X.shape[0]))
+    v = X.data.astype(np.float64) * scale[X.indices]
+    rows = np.repeat(np.arange(X.shape[0]), np.diff(X.indptr))
+    v /= np.bincount(rows, weights=v)[rows]
+    return X.with_data(v.astype(np.float32))
+
+
+@pytest.mark.parametrize("decades", [4, 9, 14, 18])
+def test_entries_of_very_different_size_without_a_prune(decades):
+    """Every entry is kept: entries far below the row's sum are as accurate as
+    FP32 sums."""
+    X = _scaled_columns(decades, 13)
+    check_mcl_step(X, _run(X, r=1, prune=0.0, topk=1000), 1, 0.0, 1000)
+
+
+def test_rows_of_zeros_and_underflow():
+    """Rows whose stored values are zero, and rows whose inflated values
+    underflow, have no entries, as in the hash kernel; their neighbours are
+    the oracle's."""
+    X = _clusters([64] * 12, 17)
+    v = X.data.copy()
+    zero, tiny = np.arange(0, X.shape[0], 5), np.arange(1, X.shape[0], 5)
+    for i in zero:
+        v[X.indptr[i]:X.indptr[i + 1]] = 0.0
+    for i in tiny:
+        v[X.indptr[i]:X.indptr[i + 1]] *= 1e-30
+    X = X.with_data(v)
+    got = _run(X, r=2, prune=1e-4, topk=1000)
+    lens = np.diff(got.indptr)
+    assert not lens[zero].any() and not lens[tiny].any()
+    check_mcl_step(X, got, 2, 1e-4, 1000, rows=np.arange(2, X.shape[0], 5))
