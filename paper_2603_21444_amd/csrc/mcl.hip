@@ -295,8 +295,16 @@ __global__ __launch_bounds__(MGeom<G>::WG) void k_mcl_rows(
 // kMclPending), and so is one that FP32 sums serve better: an entry's error is
 // half a unit (2^-61 of the row's bound at most) per product, so a kept entry
 // of less than 2^24 units could lose more than FP32 sums do; and rows whose
-// sum is zero or whose products may not be finite.  When a quarter of the rows taken so far were given back, the
-// rest of the bin is left to that kernel.
+// sum is zero or whose products may not be finite.
+//
+// Which bins are tried: 64 rows spread over a bin's list are looked at
+// beforehand (k_row_abs), and where more than a quarter of them have too many
+// columns the whole bin is left to k_mcl_rows; so is the rest of a bin when a
+// quarter of the rows taken so far came back.  Without the look up to 16384
+// rows of a bin (eight a block) are under way before one comes back: on 2^19
+// unclustered vertices (MCL iterations 1, 6 and 7, prune 1e-4) 0.3 ms a bin,
+// and 7.1 ms for rows of 8193..16384 products while a row with too many
+// columns also filled the table and walked it.
 //
 // k_mcl_rows sizes its table by the products, holds one row per CU, and its
 // float compare-and-swap adds collide.  2^16 rows in clusters of 64 (4356
@@ -306,10 +314,65 @@ __global__ __launch_bounds__(MGeom<G>::WG) void k_mcl_rows(
 constexpr int kFewNT = 256;
 constexpr int kFewSlots = 1024;
 constexpr int kFewCols = 512;
+static_assert(kFewCols + kFewNT < kFewSlots, "a slot stays empty");
 constexpr int kFewWords = 256;  // marks of 8192 products at a time
-constexpr int kFewBin = 6;      // first bin tried: more than 256 products
+constexpr int kFewBin = 6;      // first bin tried: 257..512 products, which always fit
+constexpr int kFewSample = 64;  // rows of a bin looked at beforehand
+constexpr int kFewLook = 1024;  // products of such a row
 constexpr int kFewTry = 512;    // rows taken before the share given back counts
 constexpr int kFewTake = 8;     // rows per atomic on the queue (12 ns each on one word)
+constexpr size_t kFewSampleAt = 2048;  // the sample's answers in the workspace, below the row bins
+static_assert(kFewSample == kWave, "one answer a lane");
+static_assert(kFewSampleAt + (kMaxLdsBin - kFewBin + 1) * kFewSample * 4 <= 4096 &&
+                  256 + sizeof(Problem) <= kFewSampleAt,
+              "room behind the header and the operand descriptors");
+
+// Whether the table holds more than kFewCols columns.  The number is read anew
+// before every column that enters, so at most one per thread enters past it:
+// the table never fills, and walks stay short in rows that are given back.
+__device__ __forceinline__ bool few_full(const int *ncols) {
+  return __hip_atomic_load(ncols, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) > kFewCols;
+}
+
+// The slot of a column from slot h on, taken if need be.
+__device__ __forceinline__ uint32_t few_slot(int col, uint32_t h, int *key, int *ncols) {
+  for (int probes = 0; probes < kFewSlots; ++probes) {
+    int k = key[h];
+    if (k == kEmpty) {
+      k = atomicCAS(&key[h], kEmpty, col);
+      if (k == kEmpty) atomicAdd(ncols, 1);
+    }
+    if (k == kEmpty || k == col) break;
+    h = (h + 1) & (kFewSlots - 1);
+  }
+  return h;
+}
+
+// Whether row i has more than kFewCols columns (1), by its first products (at
+// least kFewLook, or all): one block, its table and counter.
+__device__ __forceinline__ int few_look(const Part &P, int i, int *key, int *ncols) {
+  const int tid = threadIdx.x, lane = lane_id();
+  if (tid == 0) *ncols = 0;
+  for (int s = tid; s < kFewSlots; s += kFewNT) key[s] = kEmpty;
+  __syncthreads();
+  int as, ae;
+  a_row(P, i, as, ae);
+  const int nA = ae - as;
+  int seen = 0;
+  for (int e = tid / kWave; e < nA && seen < kFewLook / (kFewNT / kWave);
+       e += kFewNT / kWave) {
+    const int k = gp(P.acol)[as + e];
+    const int b0 = gp(P.brp)[k], len = gp(P.brp)[k + 1] - b0;
+    for (int q = lane; q < len; q += kWave) {
+      const int col = gp(P.bcol)[b0 + q];
+      const uint32_t h = scramble_slot((uint32_t)col, 10);
+      if (key[h] != col && !few_full(ncols)) (void)few_slot(col, h, key, ncols);
+    }
+    seen += len;
+  }
+  __syncthreads();
+  return *ncols > kFewCols ? 1 : 0;
+}
 
 struct FewEntry {
   float a;
@@ -320,7 +383,7 @@ __global__ __launch_bounds__(kFewNT, 8) void k_mcl_few(
     const Problem *__restrict__ pr, const int32_t *__restrict__ rows, WsHeader *__restrict__ hdr,
     int bin, int r, int rpost, float prune, int topk, int cap, const double *__restrict__ rabs,
     int32_t *__restrict__ ycol, float *__restrict__ yval, int32_t *__restrict__ ycnt,
-    int32_t *__restrict__ failed) {
+    int32_t *__restrict__ failed, const int32_t *__restrict__ sample) {
   __shared__ unsigned long long acc[kFewSlots];
   __shared__ int key[kFewSlots];
   __shared__ FewEntry ent[kFewNT];
@@ -336,6 +399,11 @@ __global__ __launch_bounds__(kFewNT, 8) void k_mcl_few(
   const int count = hdr->bin_count[bin];
   const int start = hdr->bin_start[bin];
   const int tid = threadIdx.x;
+  {
+    const int looked = min(count, kFewSample), lane = lane_id();
+    const int wide = lane < looked ? sample[(bin - kFewBin) * kFewSample + lane] : 0;
+    if (__popcll(__ballot(wide)) * 4 > looked) return;  // left to k_mcl_rows
+  }
   const Part &P = pr->part[0];
   const SPG_GLOBAL int32_t *brp = gp(P.brp);
   const SPG_GLOBAL int32_t *bcol = gp(P.bcol);
@@ -399,7 +467,7 @@ __global__ __launch_bounds__(kFewNT, 8) void k_mcl_few(
       const int off = group_excl_scan<true, kFewNT>(len, tid, wtot, tot);
       const int rank = group_excl_scan<true, kFewNT>(len > 0 ? 1 : 0, tid, wtot, live);
       if (len > 0) ent[rank] = FewEntry{a, b0 - off};
-      for (int w0 = 0; w0 < tot; w0 += kFewWords * 32) {
+      for (int w0 = 0; w0 < tot && ncols <= kFewCols; w0 += kFewWords * 32) {
         // bit p - w0: product p is the last of its entry
         mark[tid] = 0u;
         __syncthreads();
@@ -433,17 +501,7 @@ __global__ __launch_bounds__(kFewNT, 8) void k_mcl_few(
           for (int u = 0; u < U; ++u) {
             if (!in[u]) continue;
             uint32_t h = scramble_slot((uint32_t)col[u], 10);
-            // at most one walk round the table (it can fill up before every
-            // thread sees that the row is given back)
-            for (int probes = 0; probes < kFewSlots; ++probes) {
-              int k = key[h];
-              if (k == kEmpty) {
-                k = atomicCAS(&key[h], kEmpty, col[u]);
-                if (k == kEmpty) atomicAdd(&ncols, 1);
-              }
-              if (k == kEmpty || k == col[u]) break;
-              h = (h + 1) & (kFewSlots - 1);
-            }
+            if (key[h] != col[u] && !few_full(&ncols)) h = few_slot(col[u], h, key, &ncols);
             const long long q = __double2ll_rn((double)(en[u].a * v[u]) * sigma);
             atomicAdd(&acc[h], (unsigned long long)q);
           }
@@ -1241,18 +1299,35 @@ __global__ __launch_bounds__(kPT, kPT / 256) void k_mcl_panel(
 }
 
 // Row sums of |x| in FP64 (the bound behind the fixed-point scales); clears
-// the counts of rows given back by k_mcl_few.
+// the counts of rows given back by k_mcl_few.  The first `looks` blocks look at
+// rows spread over the lists of the bins from kFewBin on (64 a bin) instead: a
+// launch of their own would cost more than they do.
 __global__ __launch_bounds__(256) void k_row_abs(const Problem *__restrict__ pr,
+                                                 const int32_t *__restrict__ rows,
                                                  const WsHeader *__restrict__ hdr,
                                                  double *__restrict__ rabs,
-                                                 int32_t *__restrict__ failed) {
+                                                 int32_t *__restrict__ failed, int looks,
+                                                 int32_t *__restrict__ sample) {
+  static_assert(kFewNT == 256, "few_look's block");
+  __shared__ int key[kFewSlots];
+  __shared__ int ncols;
   if (hdr->status) return;
-  if (blockIdx.x == 0 && threadIdx.x < kNB) failed[threadIdx.x] = 0;
+  if ((int)blockIdx.x < looks) {
+    const int b = kFewBin + blockIdx.x / kFewSample, s = blockIdx.x % kFewSample;
+    const int count = hdr->bin_count[b], looked = min(count, kFewSample);
+    if (s >= looked) return;
+    const int at = (int)((int64_t)s * count / looked);
+    const int wide = few_look(pr->part[0], rows[hdr->bin_start[b] + at], key, &ncols);
+    if (threadIdx.x == 0) sample[blockIdx.x] = wide;
+    return;
+  }
+  const int block = blockIdx.x - looks;
+  if (block == 0 && threadIdx.x < kNB) failed[threadIdx.x] = 0;
   const Part &P = pr->part[0];
   const int n = P.kdim;
   const int lane = lane_id();
-  const int64_t wv = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave;
-  const int64_t nwv = ((int64_t)gridDim.x * blockDim.x) / kWave;
+  const int64_t wv = ((int64_t)block * blockDim.x + threadIdx.x) / kWave;
+  const int64_t nwv = ((int64_t)(gridDim.x - looks) * blockDim.x) / kWave;
   const SPG_GLOBAL float *bval = gp(static_cast<const float *>(P.bval));
   for (int64_t k = wv; k < n; k += nwv) {
     const int s = gp(P.brp)[k], e = gp(P.brp)[k + 1];
@@ -1314,15 +1389,21 @@ hipError_t launch_mcl(const Problem *dpr, const BinPlan &bp, const WsLayout &L, 
   double *rabs = reinterpret_cast<double *>(ws + L.mcl_rabs);
   // rows given back per bin: the binning's histograms are no longer needed
   int32_t *failed = reinterpret_cast<int32_t *>(ws + L.blockhist);
-  hipLaunchKernelGGL(k_row_abs, dim3(D.cus * 8), dim3(256), 0, st, dpr, hdr, rabs, failed);
+  int32_t *sample = reinterpret_cast<int32_t *>(ws + kFewSampleAt);
+  int looks = 0;
+  for (int b = kFewBin; b <= bp.maxbin; ++b)
+    if (!bp.known || bp.count[b] >= D.cus) looks = (b - kFewBin + 1) * kFewSample;
+  hipLaunchKernelGGL(k_row_abs, dim3(std::max(D.cus * 8, 2 * looks)), dim3(256), 0, st, dpr, rows,
+                     hdr, rabs, failed, looks, sample);
   for (int b = 1; b <= bp.maxbin; ++b) {
     if (bp.known && bp.count[b] == 0) continue;
-    // a row of this many products may fall on few columns
-    const bool few = b >= kFewBin;
+    // a row of this many products may fall on few columns; not worth two
+    // launches where every row has a CU (23 rows: 0.06 ms against 0.03)
+    const bool few = b >= kFewBin && !(bp.known && bp.count[b] < D.cus);
     if (few) {
       const int grid = bp.known ? std::min(D.cus * 8, bp.count[b]) : D.cus * 8;
       hipLaunchKernelGGL(k_mcl_few, dim3(grid), dim3(kFewNT), 0, st, dpr, rows, hdr, b, r, rpost,
-                         prune, topk, cap, rabs, pcol, pval, ycnt, failed);
+                         prune, topk, cap, rabs, pcol, pval, ycnt, failed, sample);
     }
     int G = bp.lanes[b] < 8 ? 8 : bp.lanes[b];  // no one-thread-per-row MCL kernel
     while (G < 1024 && mcl_lds_bytes(b, G) > D.lds_per_block) G *= 2;

@@ -111,3 +111,54 @@ def test_rows_of_zeros_and_underflow():
     lens = np.diff(got.indptr)
     assert not lens[zero].any() and not lens[tiny].any()
     check_mcl_step(X, got, 2, 1e-4, 1000, rows=np.arange(2, X.shape[0], 5))
+
+
+def _rows_of(n, d, seed, clustered):
+    """n rows of d entries: clusters of d vertices (labels shuffled) for the
+    rows in `clustered`, d random columns for the others."""
+    rng = synth.rng_for(seed, 6)
+    label = rng.permutation(n)
+    at = np.argsort(label)
+    cols = np.sort(label[np.minimum(at // d * d, n - d)[:, None] + np.arange(d)], axis=1)
+    wide = np.ones(n, dtype=bool)
+    wide[clustered] = False
+    for i in np.nonzero(wide)[0]:
+        cols[i] = np.sort(rng.choice(n, size=d, replace=False))
+    w = 0.5 + 0.5 * rng.random((n, d))
+    w /= w.sum(1, keepdims=True)
+    return synth.HostCSR((n, n), np.arange(n + 1, dtype=np.int64) * d,
+                         cols.astype(np.int32).ravel(), w.astype(np.float32).ravel())
+
+
+@pytest.mark.parametrize("share", [0.0, 0.5, 0.85, 0.97])
+def test_bins_of_few_and_many_columns(share):
+    """20000 rows of 2500 products in one bin, none, half or most of them of
+    rows in clusters (whose products still spread where a row of the cluster is
+    a random one): every row is the oracle's, whichever kernel takes it."""
+    n = 20000
+    X = _rows_of(n, 50, 21, np.arange(int(share * n)) if share < 0.9 else
+                 np.nonzero(synth.rng_for(1, 7).random(n) < share)[0])
+    check_mcl_step(X, _run(X, r=2, prune=1e-4, topk=300), 2, 1e-4, 300)
+
+
+@pytest.mark.parametrize("columns", [511, 512, 513])
+def test_rows_of_one_bin_at_the_limit_of_columns(columns):
+    """400 rows of 20 entries, each a row with the same `columns` columns (all
+    empty rows): 10240 products on at most, or just more than, 512 columns."""
+    rng = synth.rng_for(columns, 4)
+    n, hubs = 2000, 30
+    at = rng.permutation(n)
+    hub, body, cols = at[:hubs], at[hubs:hubs + 400], np.sort(at[hubs + 400:hubs + 400 + columns])
+    rows = [np.zeros(0, dtype=np.int64)] * n
+    for v in hub:
+        rows[v] = cols
+    for v in body:
+        rows[v] = np.sort(rng.choice(hub, size=20, replace=False))
+    ip = np.concatenate([[0], np.cumsum([r.size for r in rows])]).astype(np.int64)
+    v = 0.5 + 0.5 * rng.random(int(ip[-1]))
+    lens = np.diff(ip)
+    X = synth.HostCSR((n, n), ip, np.concatenate(rows).astype(np.int32),
+                      (v / np.repeat(lens, lens)).astype(np.float32))
+    got = _run(X, r=2, prune=0.0, topk=1000)
+    assert set(np.diff(got.indptr)[body].tolist()) == {columns}
+    check_mcl_step(X, got, 2, 0.0, 1000)
