@@ -670,6 +670,13 @@ constexpr int kCPT = kPanel / kPT;  // panel columns per thread in the epilogue
 // groups for the first: 1 to 4 % slower).
 constexpr int kPUDense = 5, kPUSparse = 4;
 constexpr int kPE = 1024;     // entries whose cursors stay in LDS
+static_assert(kCPT == 16, "a thread's columns are half a bitmap word");
+// Rows with fewer products per panel than this look only at the columns that
+// the bitmap marks, two passes over them, instead of at all 16 of a thread:
+// 10^5 and 10^4 products a row on 2^19 columns (MCL, iterations 5 and 6, the
+// second mostly of such rows) take 704 and 201 ms, 701 and 237 with all rows
+// dense; at 3072, with rows of 2500 per panel among them, 710 and 200.
+constexpr int kSparse = 1536;
 
 struct PanelRed {
   double s;
@@ -952,31 +959,73 @@ __global__ __launch_bounds__(kPT, kPT / 256) void k_mcl_panel(
                          (double)((n + kPanel - 1) / kPanel);
       while (lS < 6 && (double)(1 << lS) < per) ++lS;
     }
-    // The bitmap is kept only where it matters: with a prune above zero a
-    // column whose sum is zero is dropped like an absent one.  A row
-    // whose sums are all zero is taken once more, with it.
+    // rows of few products per panel: only the marked columns are looked at
+    const bool sparse = (double)R.total < (double)kSparse * ((n + kPanel - 1) / kPanel);
+    // The bitmap is kept only where it matters: for such rows; with a prune
+    // above zero a column whose sum is zero is dropped like an absent one.  A
+    // row whose sums are all zero is taken once more, with it.
     const int mfirst = R.mn;
     double scum;
     float S;
     int nc, nk, kept0;
     uint32_t bbits;
     int bcolumn;
-    bool track = !(prune > 0.f);
+    bool track = sparse || !(prune > 0.f);
     while (true) {
       int mnext = mfirst;
       scum = 0.0;
       nc = 0;
       bbits = 0u;
       bcolumn = -1;
-      while (mnext < n) {
-        const int plo = mnext & ~(kPanel - 1);
-        const uint32_t width = plo < 0 ? 0u : (uint32_t)min(kPanel, n - plo);
 #define SPG_ACC(PU, LS, TRACK)                                                              \
   panel_accumulate<PU, LS, TRACK>(bcol, bval, s_cur, s_end, s_val, nA, sigma, plo, width, pacc, \
                                   pbm)
 #define SPG_ACC_G(PU, LS)                                                                     \
   panel_accumulate<PU, LS, true>(bcol, bval, gpw(ecur), gpw(eend), gpw(evalg), nA, sigma, plo, \
                                  width, pacc, pbm)
+      while (sparse && mnext < n) {
+        const int plo = mnext & ~(kPanel - 1);
+        const uint32_t width = plo < 0 ? 0u : (uint32_t)min(kPanel, n - plo);
+        const int tmn = !lds_state ? SPG_ACC_G(kPUSparse, 3)
+                        : lS >= 5  ? SPG_ACC(kPUDense, 5, true)
+                                   : SPG_ACC(kPUSparse, 3, true);
+        __syncthreads();
+        const float low = even ? (float)((double)prune * scum * (1.0 - 1.0 / 1024.0)) : -INFINITY;
+        // thread t: the marked ones of columns 16 t .. 16 t + 15
+        const uint32_t marked = pbm[tid >> 1] >> ((tid & 1) * 16) & 0xffffu;
+        double ps = 0.0;
+        int cnt = 0;
+        for (uint32_t b = marked; b; b &= b - 1) {
+          const int cl = tid * kCPT + __ffs(b) - 1;
+          const float p = ipow((float)((double)(long long)pacc[cl] * inv_sigma), r);
+          ps += (double)p;
+          if (__float_as_uint(p) > bbits || bcolumn < 0) {  // ties: the smaller column came first
+            bbits = __float_as_uint(p);
+            bcolumn = plo + cl;
+          }
+          cnt += p >= low ? 1 : 0;
+        }
+        R = panel_reduce(ps, cnt, tmn, 0ull, rs, rc, rm, rb);
+        int o = nc + R.excl;
+        for (uint32_t b = marked; b; b &= b - 1) {
+          const int cl = tid * kCPT + __ffs(b) - 1;
+          const float p = ipow((float)((double)(long long)pacc[cl] * inv_sigma), r);
+          pacc[cl] = 0ull;
+          if (p >= low) {
+            lcol[o] = plo + cl;
+            lval[o] = p;
+            ++o;
+          }
+        }
+        if ((tid & 1) == 0) pbm[tid >> 1] = 0u;
+        scum += R.s;
+        nc += R.total;
+        mnext = R.mn;
+        __syncthreads();
+      }
+      while (mnext < n) {
+        const int plo = mnext & ~(kPanel - 1);
+        const uint32_t width = plo < 0 ? 0u : (uint32_t)min(kPanel, n - plo);
         int tmn;
         if (!lds_state) {  // the bitmap does no harm where it is not needed
           tmn = lS >= 5 ? SPG_ACC_G(kPUDense, 5) : SPG_ACC_G(kPUSparse, 3);
@@ -991,8 +1040,6 @@ __global__ __launch_bounds__(kPT, kPT / 256) void k_mcl_panel(
             default: tmn = SPG_ACC(kPUSparse, 2, false); break;
           }
         }
-#undef SPG_ACC_G
-#undef SPG_ACC
         __syncthreads();
         // a product that is zero cannot survive a prune above zero
         const float thr = (float)((double)prune * scum * (1.0 - 1.0 / 1024.0));
@@ -1037,6 +1084,8 @@ __global__ __launch_bounds__(kPT, kPT / 256) void k_mcl_panel(
         // the next panel's first barrier, or that of the code below
         if (track || !lds_state) __syncthreads();
       }
+#undef SPG_ACC_G
+#undef SPG_ACC
       // values that the exact test keeps, per wave (a run of the list each)
       __syncthreads();
       S = (float)scum;

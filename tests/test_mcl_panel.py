@@ -35,3 +35,43 @@ def test_rows_emptied_by_the_prune(order, r, prune, strong):
     check_mcl_step(X, got, r, prune, 100, order=order, rows=np.arange(0, 4000, 20))
     if not strong and (order == "paper" or r < 3):  # (the cube lifts entries over the prune)
         assert (np.diff(got.indptr) == 1).mean() > 0.9
+
+
+def _few_per_panel(n, entries, length, seed, zero=()):
+    """60 rows of `entries` entries, each a row of `length` random columns of
+    n; the rows in `zero` point to rows of zeros; all other rows are empty."""
+    rng = synth.rng_for(seed, 4)
+    hubs = 2 * entries
+    rows = [np.zeros(0, dtype=np.int64)] * n
+    vals = [np.zeros(0)] * n
+    at = rng.permutation(n)[:hubs + 60]
+    hub, zeros = at[:hubs - entries // 2], at[hubs - entries // 2:hubs]
+    for v in at[:hubs]:
+        rows[v] = np.sort(rng.choice(n, size=length, replace=False))
+        vals[v] = (0.5 + rng.random(length)) * (0.0 if v in set(zeros.tolist()) else 1.0)
+    body = at[hubs:]
+    for t, v in enumerate(body):
+        pick = np.concatenate([zeros, zeros]) if t in zero else hub
+        pick = np.unique(pick)
+        rows[v] = np.sort(rng.choice(pick, size=min(entries, pick.size), replace=False))
+        vals[v] = 0.5 + rng.random(rows[v].size)
+    ip = np.concatenate([[0], np.cumsum([r.size for r in rows])]).astype(np.int64)
+    v = np.concatenate([x / max(x.sum(), 1e-30) for x in vals])
+    return synth.HostCSR((n, n), ip, np.concatenate(rows).astype(np.int32), v.astype(np.float32)), body
+
+
+@pytest.mark.parametrize("entries,length", [(200, 100), (40, 600), (1500, 12)])
+@pytest.mark.parametrize("order,r,prune,topk", [("workload", 2, 1e-5, 10000), ("workload", 3, 1e-9, 500),
+                                                ("workload", 2, 0.0, 300), ("paper", 2, 4e-5, 300),
+                                                ("paper", 2, 0.5, 100)])
+def test_few_products_per_panel(entries, length, order, r, prune, topk):
+    """Some 20000 products on 300000 columns (19 panels): only the marked
+    columns are looked at; entries in LDS and in the slot scratch, all order
+    and prune combinations, rows that the prune empties."""
+    X, body = _few_per_panel(300000, entries, length, entries)
+    got = _run(X, r=r, prune=prune, topk=topk, order=order)
+    lens = np.diff(got.indptr)
+    assert lens[body].all()
+    if prune == 0.5:
+        assert (lens[body] == 1).all()
+    check_mcl_step(X, got, r, prune, topk, order=order, rows=np.sort(body))
