@@ -24,7 +24,7 @@
 // kernels that walked the row part by part, a wave each: 8 uniform blocks,
 // 2^18 rows of 2600 products: numeric 7.20 -> 6.24 ms (4.9 without the ranks,
 // 3.9 without ranks and stores, 2.75 without the gathers either), count 3.31
-// -> 2.56; 1025..2048 products 0.67 -> 0.51 and 0.33 -> 0.22.  R-MAT blocks:
+// -> 2.56; 1025..2048 products 0.67 -> 0.45 and 0.33 -> 0.22.  R-MAT blocks:
 // numeric 0.72 + 0.60 -> 0.41 + 0.45 ms, count 0.53 + 0.41 + 0.25 -> 0.18 +
 // 0.20 + 0.11 ms.
 #include <algorithm>
@@ -155,9 +155,14 @@ __device__ __forceinline__ int blk_chunk(BlkLds<NT, VT> &s, int K, const BlkHead
 }
 
 // Waves per SIMD the kernel is compiled for (bounds its registers): three
-// blocks of 512 threads fit a CU's LDS with FP32 values.
+// blocks of 512 threads fit a CU's LDS with FP32 values, six of 256, of which
+// five get by without spills (8 uniform blocks, rows of 1025..2048 products:
+// 0.45 ms, 0.47 at six, 0.50 at four; rows of 1300 products in bands, sorted as
+// a whole: 5.54, 5.03 and 6.59, 5.35 now).
 template <int NT, typename VT>
-constexpr int blk_waves() { return NT == 512 && sizeof(VT) == 4 ? 6 : 4; }
+constexpr int blk_waves() {
+  return sizeof(VT) == 8 || NT == 1024 ? 4 : NT == 512 ? 6 : 5;
+}
 
 template <int NT, typename VT>
 __global__ __launch_bounds__(NT, (blk_waves<NT, VT>())) void k_num_block(
@@ -218,7 +223,9 @@ __global__ __launch_bounds__(NT, (blk_waves<NT, VT>())) void k_num_block(
     BlkHead<VT> nx;
     nx.i = blk_row(list, item, count);
     // tickets
-    // (above the column; one too large to fit belongs to a row that is sorted)
+    // (above the column; one too large to fit belongs to a row that is sorted;
+    // leaving out half of them once a bucket is large: clustered rows 1 %
+    // faster, others 3.5 % slower)
 #pragma unroll
     for (int j = 0; j < kBlkE; ++j) {
       if (col[j] >= 0) {

@@ -146,8 +146,53 @@ __device__ void lds_sort_pairs(uint32_t *key, VT *val, int P, int t) {
   int ln = 0;
   while ((1 << ln) < P) ++ln;
   const int half = (1 << ln) >> 1;
+  int lk0 = 1;
+  if (BLOCK) {
+    // merges of 2, 4 and 8: eight consecutive elements in registers, one pass
+    // over LDS instead of six (rows of 1300 products in bands, numeric pass:
+    // 5.54 -> 5.35 ms)
+    for (int c0 = 8 * t; c0 < P; c0 += 8 * NT) {
+      uint32_t k[8];
+      VT v[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const bool in = c0 + e < P;
+        k[e] = in ? key[c0 + e] : 0xffffffffu;
+        v[e] = in ? val[c0 + e] : VT(0);
+      }
+      auto order = [&](int a, int b) {
+        const bool swap = k[a] > k[b];
+        const uint32_t ka = k[a];
+        const VT va = v[a];
+        k[a] = swap ? k[b] : ka;
+        k[b] = swap ? ka : k[b];
+        v[a] = swap ? v[b] : va;
+        v[b] = swap ? va : v[b];
+      };
+#pragma unroll
+      for (int s = 2; s <= 8; s <<= 1) {
+#pragma unroll
+        for (int a = 0; a < 8; ++a)  // mirrored positions of a block of s
+          if (a < (a ^ (s - 1))) order(a, a ^ (s - 1));
+#pragma unroll
+        for (int d = s / 4; d > 0; d >>= 1)
+#pragma unroll
+          for (int a = 0; a < 8; ++a)
+            if ((a & d) == 0) order(a, a + d);
+      }
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        if (c0 + e < P) {
+          key[c0 + e] = k[e];
+          val[c0 + e] = v[e];
+        }
+      }
+    }
+    group_sync<BLOCK>();
+    lk0 = 4;
+  }
   // block sizes and distances are powers of two: shifts and masks, no division
-  for (int lk = 1; lk <= ln; ++lk) {
+  for (int lk = lk0; lk <= ln; ++lk) {
     const int k = 1 << lk;
     for (int lj = lk - 1; lj >= 0; --lj) {
       const int j = 1 << lj;

@@ -59,3 +59,25 @@ def test_rows_at_the_edges_of_the_bins(n, width, blen, parts, dtype):
     got = binding.batched([(binding.to_device(a), binding.to_device(b)) for a, b in got_in]).to_host()
     ref, S = oracle.spgemm(A.astype(np.float64), Bm.astype(np.float64), with_abs=True)
     assert_same_csr(got, ref, S, dtype, exact=True, what=f"n={n} width={width} parts={parts}")
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("width", [36, 50, 63, 64])
+def test_rows_sorted_as_a_whole(width, dtype):
+    """Rows of about width^2 products on few neighbouring columns, many or none
+    of them repeated, with products past the last multiple of eight."""
+    from paper_2603_21444_amd import binding
+    rng = synth.rng_for(width, 11)
+    n, k, m = 1 << 20, 70, 40
+    rows = [np.sort(rng.choice(5000, size=width - t % 3, replace=False)) + 300000 for t in range(k)]
+    rows += [np.arange(width - t % 3) + 700000 + width * t for t in range(k)]  # no repeats
+    ip = np.concatenate([[0], np.cumsum([r.size for r in rows])]).astype(np.int64)
+    B = synth.HostCSR((2 * k, n), ip, np.concatenate(rows).astype(np.int32),
+                      rng.integers(-3, 4, size=ip[-1]).astype(dtype))
+    pick = [h * k + rng.choice(k, size=width, replace=False) for h in (0, 1) for _ in range(m)]
+    A = synth.HostCSR((2 * m, 2 * k), np.arange(2 * m + 1, dtype=np.int64) * width,
+                      np.concatenate(pick).astype(np.int32),
+                      rng.integers(-3, 4, size=2 * m * width).astype(dtype))
+    got = binding.spgemm(binding.to_device(A), binding.to_device(B)).to_host()
+    ref, S = oracle.spgemm(A.astype(np.float64), B.astype(np.float64), with_abs=True)
+    assert_same_csr(got, ref, S, dtype, exact=True)
