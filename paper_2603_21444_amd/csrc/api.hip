@@ -308,16 +308,15 @@ BinPlan make_binplan(spg_plan p, int maxbin, bool counts_known, const int *count
   return bp;
 }
 
-// Whether B's columns and values are worth laying side by side (k_pair_b):
-// every A entry then gathers one line less, and an entry of B costs 16 bytes
-// once.  An aggregation operator (16 A entries per B entry, 2^20 x 2^17)
+// Whether B's columns and values are worth laying side by side (k_pair_b) for
+// the FP32 register sort: every A entry then gathers one line less, and an
+// entry of B costs 16 bytes once.  An aggregation operator (16 A entries per B entry, 2^20 x 2^17)
 // gains, 1.13 -> 0.93 ms; with as many A entries as B entries unstructured
 // rows still do (2^20 rows of 16 x 16: 2.02 -> 1.93 ms), but rows in bands or
 // with hubs, whose lines stay in the caches, lose (2.06 -> 2.21, R-MAT stages
 // 6.88 -> 7.07 ms), so the line lies at twice as many.  Not for sums (each
 // operand row is read once), nor for operands that stay in an L2 of 4 MB.
-// The words take up to an eighth of the heavy rows' region.  Returns the
-// bytes, 0 for none.
+// Returns the bytes, 0 for none.
 size_t pair_bytes(int K, const spg_csr *A, const spg_csr *B) {
   if (!A) return 0;
   int64_t na = 0, nb = 0;
@@ -328,6 +327,29 @@ size_t pair_bytes(int K, const spg_csr *A, const spg_csr *B) {
   return na >= 2 * nb && nb * 8 >= (4 << 20) ? (size_t)nb * 8 : 0;
 }
 
+// Whether rows of a product take the register sort, the only reader of the
+// words (two million of them cost 6 us, and the slots their room takes).
+bool any_sort_rows(const BinPlan &bp) {
+  for (int b = 1; b < kNB; ++b)
+    if (sort_rows_ok(b, bp.n) && !(b == 1 && bp.lanes[b] == 1) && (!bp.known || bp.count[b] > 0))
+      return true;
+  return false;
+}
+
+// Room for the words at the end of the heavy rows' region, whose offsets stay
+// as they are: up to an eighth of the slots, so at most 32 n entries of B
+// where all 256 slots are there (none in a call with few slots).
+void pair_room(WsLayout &L, size_t bytes, int n) {
+  const size_t slot = (size_t)(std::max(n, 1) + 4) * 8;
+  const size_t less = (bytes + 255 + slot - 1) / slot;
+  if (less > (size_t)L.heavy_slots / 8) return;
+  L.pair_slots = (int)less;
+  L.heavy_slots -= (int)less;
+  L.pairs = align256(L.heavyacc + (size_t)L.heavy_slots * slot);
+  const size_t acc = (size_t)L.heavy_slots * slot;
+  L.split_pcap = std::min(L.split_pcap, (int64_t)(acc > 512 ? (acc - 512) / 12 : 0));
+}
+
 // Shared symbolic sequence for products (identity == false) and merges.
 int run_symbolic(spg_plan p, const Problem &pr, const spg_csr *A, const spg_csr *B,
                  int32_t *C_row_ptr, int64_t *C_nnz_host, int64_t capacity, void *workspace,
@@ -336,20 +358,8 @@ int run_symbolic(spg_plan p, const Problem &pr, const spg_csr *A, const spg_csr 
   const int heavy = heavy_override > 0         ? heavy_override
                     : p->tun.heavy_slots > 0 ? p->tun.heavy_slots
                                              : default_heavy_slots(n);
-  WsLayout L = ws_layout(m, n, heavy);
+  const WsLayout L = ws_layout(m, n, heavy);
   if (!workspace || ws_bytes < L.total) return SPG_ERR_WORKSPACE;
-  if (const size_t pb = pair_bytes(pr.K, A, B)) {
-    // fewer concurrent heavy rows make room for the words behind the layout
-    const size_t slot = (size_t)(std::max(n, 1) + 4) * 8;
-    const size_t less = (pb + slot - 1) / slot;
-    if (less <= (size_t)heavy / 8) {
-      const WsLayout S = ws_layout(m, n, heavy - (int)less);
-      if (S.total + pb <= ws_bytes) {
-        L = S;
-        L.pairs = S.total;
-      }
-    }
-  }
   if (!C_nnz_host && capacity < 0) return SPG_ERR_ARG;
   const bool eager = C_nnz_host != nullptr;
   const bool clear = eager || p->status_ws != workspace;
@@ -404,8 +414,11 @@ int run_symbolic(spg_plan p, const Problem &pr, const spg_csr *A, const spg_csr 
   } else {
     sbp = make_binplan(p, D.sym_maxbin, false, nullptr, true);
   }
+  const size_t pb = pair_bytes(pr.K, A, B);
+  if (pb && any_sort_rows(sbp)) pair_room(p->L, pb, n);
+  sbp.heavy_slots = p->L.heavy_slots;
   // a3: exact row counts, then the scan into row_ptr
-  e = launch_symbolic_bins(dpr, sbp, L, ws, C_row_ptr, st);
+  e = launch_symbolic_bins(dpr, sbp, p->L, ws, C_row_ptr, st);
   if (e != hipSuccess) return SPG_ERR_HIP;
   e = launch_scan(C_row_ptr, m, eager ? -1 : capacity, L, ws, st);
   if (e != hipSuccess) return SPG_ERR_HIP;
@@ -505,6 +518,7 @@ int run_numeric(spg_plan p, Problem &pr, spg_dtype dtype, int32_t *C_col_idx,
   if (e != hipSuccess) return SPG_ERR_HIP;
   const int maxbin = dtype == SPG_F64 ? D.num_maxbin_f64 : D.num_maxbin_f32;
   BinPlan bp = make_binplan(p, maxbin, p->counts_known, p->num_count);
+  if (dtype == SPG_F64) bp.heavy_slots += p->L.pair_slots;  // no words to keep
   if (pr.part[0].pair) {
     PairArgs a{};
     for (int k = 0; k < p->K; ++k) a.nnz[k] = p->bnnz[k];

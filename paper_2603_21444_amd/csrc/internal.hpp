@@ -30,7 +30,8 @@ struct WsLayout {
   // split heavy rows (staging in the heavy accumulator region); split_F == 0: off
   size_t split_ctl = 0, split_rows = 0, split_fo = 0, split_cur = 0, split_segs = 0,
          split_items = 0;
-  size_t pairs = 0;  // words of B's columns and values (0: none)
+  size_t pairs = 0;    // words of B's columns and values (0: none), in ...
+  int pair_slots = 0;  // ... the last slots of the heavy rows' region
   int split_F = 0, split_hmax = 0, split_segcap = 0, split_itemcap = 0;
   int64_t split_pcap = 0;
   size_t mcl_rabs = 0, mcl_slots = 0;  // MCL only: row sums of |x|, heavy-row slots
