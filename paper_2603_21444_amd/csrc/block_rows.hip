@@ -287,14 +287,13 @@ __global__ __launch_bounds__(NT, (sym_blk_waves<NT>())) void k_sym_block(const P
   constexpr int LOG2T = 31 - __builtin_clz((unsigned)T);
   extern __shared__ __align__(16) int tab[];
   __shared__ BlkLds<NT, float> s;
-  __shared__ int fresh_total, item;
+  __shared__ int fresh_total;
   const int tid = threadIdx.x;
   if (hdr->status) return;
   const int count = hdr->bin_count[bin];
   const int32_t *list = rows + hdr->bin_start[bin];
   const int K = pr->K;
   blk_load_parts(pr, s);
-  if (tid == 0) item = blockIdx.x;
   __syncthreads();
   uint32_t it = blockIdx.x;
   BlkHead<float> h;
