@@ -45,10 +45,13 @@ constexpr int kRangeWords = (1 << kSplitLog2W) >> 5;  // bitmap words per range
 // dense panel.
 constexpr int kDenseMin = 1024;
 // Other segments of at most this many columns find their places from a bitmap.
-// Against the buckets, R-MAT blocks of 2^20 columns: 1.17 -> 0.94 ms; with at
-// most 2^17 columns (three blocks a CU instead of two) 1.00.
-constexpr int kMapCols = 1 << 18;
-static_assert(kMapCols % (64 * kAccumNT) == 0, "whole words per thread");
+// Against the buckets, R-MAT blocks of 2^20 columns, FP32: 1.17 -> 0.94 ms;
+// with at most 2^17 columns (three blocks a CU instead of two) 1.00.  FP64
+// keeps to 2^17, two blocks a CU: R-MAT, 2^19 rows on 2^20 / 2^17 rows on 2^22
+// columns 0.70 / 0.17 ms, with 2^18 columns and one block 0.92 / 0.24.
+template <typename VT>
+constexpr int map_cols() { return sizeof(VT) == 4 ? 1 << 18 : 1 << 17; }
+static_assert(map_cols<double>() % (64 * kAccumNT) == 0, "whole words per thread");
 
 // ---------------------------------------------------------------------------
 // Symbolic: distinct columns of every row from bin blo on (heavy rows, one
@@ -496,9 +499,10 @@ __device__ __forceinline__ void merge_buckets(int (&kc)[kBlkE], const VT (&kv)[k
 // Bitmap word w with a gap after every eight: threads that scan runs of eight
 // words do not meet on the banks.
 __device__ __forceinline__ int map_at(int w) { return w + (w >> 3); }
-constexpr int kMapWords = kMapCols / 64 + kMapCols / 512;
+template <typename VT>
+constexpr int map_words() { return map_cols<VT>() / 64 + map_cols<VT>() / 512; }
 
-// At most kSplitSeg products over at most kMapCols columns from c0 on: marked
+// At most kSplitSeg products over at most map_cols columns from c0 on: marked
 // in a bitmap, whose bits below a column are its place among the D distinct
 // ones; values summed and columns written there.
 template <typename VT, typename Next>
@@ -619,8 +623,8 @@ __global__ __launch_bounds__(kAccumNT, 4) void k_split_merge(WsHeader *__restric
   uint32_t *cnt = reinterpret_cast<uint32_t *>(ival + kSplitSeg);
   uint32_t *ikey = cnt + kSplitSeg / 2 + kBigBucket;  // room for a bucket's length either side
   unsigned long long *map = reinterpret_cast<unsigned long long *>(ival + kSplitSeg);
-  uint16_t *pre = reinterpret_cast<uint16_t *>(map + kMapWords);
-  int32_t *okey = reinterpret_cast<int32_t *>(pre + kMapWords);
+  uint16_t *pre = reinterpret_cast<uint16_t *>(map + map_words<VT>());
+  int32_t *okey = reinterpret_cast<int32_t *>(pre + map_words<VT>());
   VT *panel = reinterpret_cast<VT *>(smem_raw);
   uint32_t *bm = reinterpret_cast<uint32_t *>(panel + (1 << kSplitLog2W));
   __shared__ int wtot[kAccumNT / kWave];
@@ -666,7 +670,7 @@ __global__ __launch_bounds__(kAccumNT, 4) void k_split_merge(WsHeader *__restric
       const int got = merge_dense<VT>(stg, sg.pcount, sg.c0, sg.dcount, panel, bm, wtot, cb, vb,
                                       hdr, next);
       if (tid == 0 && got != sg.dcount) atomicOr(&hdr->status, kStatInvalid);
-    } else if (sg.c1 - sg.c0 <= kMapCols && sg.dcount <= kSplitSeg) {
+    } else if (sg.c1 - sg.c0 <= map_cols<VT>() && sg.dcount <= kSplitSeg) {
       merge_map<VT>(kc, kv, sg.pcount, sg.c0, sg.c1 - sg.c0, sg.dcount, map, pre, okey, ival, wtot,
                     cb, vb, hdr, next);
     } else {
@@ -692,7 +696,7 @@ template <typename VT>
 static size_t merge_lds() {
   const size_t buckets = (size_t)kSplitSeg * (6 + sizeof(VT)) + 2 * kBigBucket * 4;
   const size_t dense = ((size_t)sizeof(VT) << kSplitLog2W) + (size_t)kRangeWords * 4;
-  const size_t map = (size_t)kSplitSeg * (4 + sizeof(VT)) + (size_t)kMapWords * 10;
+  const size_t map = (size_t)kSplitSeg * (4 + sizeof(VT)) + (size_t)map_words<VT>() * 10;
   return std::max(map, std::max(buckets, dense));
 }
 

@@ -66,3 +66,10 @@ def test_split_rows_of_block_products(dtype):
     got = binding.batched([(binding.to_device(a), binding.to_device(b)) for a, b in parts]).to_host()
     ref, S = oracle.spgemm(A.astype(np.float64), B.astype(np.float64), with_abs=True)
     assert_same_csr(got, ref, S, dtype, exact=True, what="four blocks")
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("n", [(1 << 17) - 3, 1 << 17, (1 << 17) + 9, (1 << 18) - 1, 3 << 17])
+def test_split_rows_about_the_spans_of_the_bitmap(n, dtype):
+    """Segments of up to, and just more than, 2^17 (FP64) and 2^18 columns."""
+    test_split_rows(n, dtype)
