@@ -26,7 +26,10 @@
 // 3.9 without ranks and stores, 2.75 without the gathers either), count 3.31
 // -> 2.56; 1025..2048 products 0.67 -> 0.45 and 0.33 -> 0.22.  R-MAT blocks:
 // numeric 0.72 + 0.60 -> 0.41 + 0.45 ms, count 0.53 + 0.41 + 0.25 -> 0.18 +
-// 0.20 + 0.11 ms.
+// 0.20 + 0.11 ms.  Where it costs: B rows that stay in the caches leave the
+// numbering's barriers to wait for (count of 2^16 rows of 4096 products in
+// clusters of 64: 0.44 -> 0.50 ms, their numeric pass 7.21 -> 7.08; 2^15 rows of
+// 4000 products of one block product: 0.51 -> 0.54 and 1.16 -> 1.00).
 #include <algorithm>
 
 #include "block_ops.hpp"

@@ -25,7 +25,8 @@
 // atomics a product and, one block a CU, the chain to a row's products.
 // R-MAT blocks, 2^20 rows, 8 parts: count 1.29 -> 0.86 ms (products spread
 // over all threads at once; the map read, counted and cleared in one sweep by
-// range; range counters in copies), scatter 1.27 -> 1.12 (one pass: a
+// range; range counters in copies; a row of 1.6 million products alone on the
+// chip 0.33 -> 0.40, its windows one after the other), scatter 1.27 -> 1.12 (one pass: a
 // product's place is its counter's old value), merge 1.41 -> 0.84.
 // A row the workspace cannot describe or stage stays with the one-block
 // heavy kernels, which take the list of such rows.
@@ -37,7 +38,9 @@
 
 namespace spg {
 
-constexpr int kSplitSymUnroll = 4;
+// A thread's products of a window loaded together (four at a time: a row of
+// 1.6 million products 0.43 ms against 0.40, R-MAT blocks 0.861 against 0.857).
+constexpr int kSplitSymUnroll = 8;
 constexpr int kScatterNT = 512;         // threads of a scatter block
 constexpr int kAccumNT = 512;           // threads of a merge block
 constexpr int kRangeWords = (1 << kSplitLog2W) >> 5;  // bitmap words per range
