@@ -322,6 +322,16 @@ int spgemm_mcl_iteration_order(spg_plan plan, const spg_csr *X, int32_t order, i
 
 /* ------------------------------------------------------------------------
  * Tuning (chosen by the autotuner outside any graph capture).
+ * Where the lanes act: the count sorts the rows of bins 1..4 in registers
+ * whatever the lanes (but for the value 1 in bin 1); from bin 5 on up to 63
+ * lanes, 64 and more select a group of lanes, one wave, one block per row (of
+ * at least 128 and 2^b threads for bin b).  The numeric pass sorts the rows of
+ * bins 1..7 in registers as long as the columns are at most 2^(29 - b); beyond
+ * that, and for other bins, more than 64 lanes select one block per row up to
+ * 2^24 columns, and lanes and sub shape the hash kernels otherwise.  sym_sub
+ * acts in the count's kernels of up to 64 lanes, sub[12] on heavy rows that are
+ * not split over many blocks.  The backward and MCL use lanes and sub
+ * throughout.
  * --------------------------------------------------------------------- */
 #define SPG_NBINS 16
 

@@ -2,14 +2,16 @@
 
 For each bin that carries a noticeable share of the work it times the
 symbolic + numeric passes (HIP events, eager, outside any graph capture)
-over a few candidate (lanes per row, lanes per A entry) pairs, then over the
-symbolic pass's own lanes per A entry, then over the bin's upper threshold
-(a fraction of the products its LDS tables are sized for: the rows above
-the threshold move to the next bin, whose tables are twice as large, so the
-threshold is also the table load factor of those rows), and keeps the
+over those candidate (lanes per row, lanes per A entry) pairs that launch
+different kernels (distinct_candidates: most bins' rows are sorted in
+registers or take a block whatever the lanes), then over the symbolic pass's
+own lanes per A entry where its kernel has any, then over the bin's upper
+threshold (a fraction of the products its LDS tables are sized for: the rows
+above the threshold move to the next bin, whose kernels hold twice as many,
+so the threshold is also the table load factor of those rows), and keeps the
 fastest; the other bins keep their current setting.  Rows beyond every LDS
-bin (heavy rows) get their lanes per A entry tuned the same way, in both
-passes.  This is the architecture-specific tuning of LDS (shared memory)
+bin (heavy rows) get their lanes per A entry tuned the same way where they
+are not split over many blocks.  This is the architecture-specific tuning of LDS (shared memory)
 use and team sizes the paper's local kernels rely on (§4.4).  Results are cached in a JSON file
 keyed by dtype, shape, number of block products and the rounded per-bin row
 histogram, so a capture reuses them without timing.
@@ -25,7 +27,8 @@ import torch
 from . import binding
 
 BIN_EDGES = [0] + [8 << b for b in range(1, 12)]
-# candidate (lanes, sub) per bin size class
+# candidate (lanes, sub) per bin size class: what a plan may be given; the tuner
+# times those that make a difference (distinct_candidates)
 CANDIDATES = {
     1: [(8, 4), (8, 8), (16, 8), (1, 1)],
     2: [(8, 8), (16, 8), (16, 16)],
@@ -41,14 +44,43 @@ CANDIDATES = {
 }
 # candidate lanes per A entry of the symbolic count
 SYM_SUB_CANDIDATES = (4, 8, 16, 32)
-# rows beyond every LDS bin (split over many blocks, or one block each):
-# their bin index and its candidate lanes per A entry, in both passes
+# rows beyond every LDS bin: their bin index and its candidate lanes per A
+# entry (of the one-block kernels)
 HEAVY_BIN = 12
 HEAVY_SUB_CANDIDATES = (16, 32, 64)
 # candidate upper thresholds of a bin, as fractions of its table capacity
 EDGE_FRACTIONS = (1.0, 0.75, 0.5)
 # the last LDS bin of the product passes keeps its full edge
 LAST_TUNED_EDGE_BIN = 10
+
+
+# rows of more columns are not split over many blocks
+SPLIT_MAX_COLUMNS = 1 << 23
+
+
+def kernels(b: int, lanes: int, sub: int, n: int) -> tuple:
+    """What the count and the numeric pass of bin b launch for `lanes` and
+    `sub` on n columns; settings that give the same are the same to both."""
+    if b == 1 and lanes == 1:
+        return ("one thread",), ("one thread",)
+    block = ("block", min(1024, max(128, lanes, 1 << b)))
+    if b <= 4:
+        count = ("register sort",)
+    else:
+        count = ("rows", lanes) if lanes < 64 else ("wave",) if lanes == 64 else block
+    if b <= 7 and n <= 1 << (29 - b):
+        return count, ("register sort",)
+    return count, block if lanes > 64 and n <= 1 << 24 else ("hash", lanes, sub)
+
+
+def distinct_candidates(b: int, n: int) -> list:
+    """The default (lanes, sub) of bin b and one candidate for every other
+    pair of kernels."""
+    t = binding.default_tuning()
+    seen = {}
+    for lanes, sub in [(t.lanes[b], t.sub[b])] + CANDIDATES[b]:
+        seen.setdefault(kernels(b, lanes, min(sub, lanes), n), (lanes, sub))
+    return list(seen.values())
 
 
 def edge_for(b: int, frac: float) -> int:
@@ -98,20 +130,22 @@ def tune(As, Bs, reps: int = 3, cache_path: str | None = None, share: float = 0.
         if key in cache:
             return _from_json(cache[key])
     t = binding.default_tuning()
+    n = Bs[0].shape[1]
     work = [counts[b] * BIN_EDGES[b] if 1 <= b <= 11 else 0 for b in range(len(counts))]
     total = sum(work) or 1
     for b in sorted(range(1, 12), key=lambda b: -work[b]):
         if work[b] < share * total:
             continue
         best, best_ms = None, float("inf")
-        for lanes, sub in CANDIDATES[b]:
+        for lanes, sub in distinct_candidates(b, n):
             t.lanes[b], t.sub[b] = lanes, sub
             ms = _time(As, Bs, t, reps)
             if ms < best_ms:
                 best, best_ms = (lanes, sub), ms
         t.lanes[b], t.sub[b] = best
         best_s = t.sym_sub[b]
-        for s in SYM_SUB_CANDIDATES:
+        has_sub = kernels(b, t.lanes[b], t.sub[b], n)[0][0] in ("rows", "wave")
+        for s in SYM_SUB_CANDIDATES if has_sub else ():
             if s == best_s:
                 continue
             t.sym_sub[b] = s
@@ -131,20 +165,19 @@ def tune(As, Bs, reps: int = 3, cache_path: str | None = None, share: float = 0.
                     best_e, best_ms = e, ms
             t.bin_edge[b] = best_e
     # heavy rows (more products than the last LDS bin of a pass holds, at
-    # least 4096 each): lanes per A entry of the numeric, then the symbolic pass
-    if HEAVY_BIN < len(counts) and counts[HEAVY_BIN] * 4096 >= share * total:
+    # least 4096 each), unless split: lanes per A entry of the numeric pass
+    if (n > SPLIT_MAX_COLUMNS and HEAVY_BIN < len(counts)
+            and counts[HEAVY_BIN] * 4096 >= share * total):
         best_ms = _time(As, Bs, t, reps)
-        for field in ("sub", "sym_sub"):
-            arr = getattr(t, field)
-            best = arr[HEAVY_BIN]
-            for s in HEAVY_SUB_CANDIDATES:
-                if s == best:
-                    continue
-                arr[HEAVY_BIN] = s
-                ms = _time(As, Bs, t, reps)
-                if ms < best_ms:
-                    best, best_ms = s, ms
-            arr[HEAVY_BIN] = best
+        best = t.sub[HEAVY_BIN]
+        for s in HEAVY_SUB_CANDIDATES:
+            if s == best:
+                continue
+            t.sub[HEAVY_BIN] = s
+            ms = _time(As, Bs, t, reps)
+            if ms < best_ms:
+                best, best_ms = s, ms
+        t.sub[HEAVY_BIN] = best
     if use_cache:
         cache[key] = _to_json(t)
         os.makedirs(os.path.dirname(path), exist_ok=True)
