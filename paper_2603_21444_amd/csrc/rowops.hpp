@@ -46,7 +46,8 @@ __device__ __forceinline__ int group_incl_scan(int v) {
   return v;
 }
 
-// The largest of the wave's values (non-negative), in its last lane.
+// The largest of the wave's values, in its last lane (negative ones too: the
+// zeros that the moves put where they have no source reach other lanes only).
 __device__ __forceinline__ int wave_max_last(int v) {
   v = max(v, (int)dpp<0x111>((uint32_t)v));
   v = max(v, (int)dpp<0x112>((uint32_t)v));
