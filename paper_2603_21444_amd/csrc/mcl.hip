@@ -308,7 +308,7 @@ __global__ __launch_bounds__(MGeom<G>::WG) void k_mcl_rows(
 //
 // k_mcl_rows sizes its table by the products, holds one row per CU, and its
 // float compare-and-swap adds collide.  2^16 rows in clusters of 64 (4356
-// products, 64 columns a row): 6.60 ms there, 1.10 here
+// products, 64 columns a row): 6.60 ms there, 1.06 here
 // (2000 vector instructions a wave and row issue 90 % of the time; one row
 // per atomic on the queue: 3.93 ms).
 constexpr int kFewNT = 256;

@@ -23,9 +23,10 @@
 // What bounds it on unstructured rows is the gathers: a random read from
 // beyond the L2 fetches a 128-byte line, at most 56 G lines/s, and every A
 // entry takes three (bounds, columns and values of its B row).  2^20 rows of
-// 256 FP32 products: 1.27 ms against 1.40 for the LDS bucket kernel this
-// replaces (0.92 with synthetic columns, 0.90 without the stores, 1.22
-// without the sort; 406 vector instructions a row against 582).  Rows that
+// 256 FP32 products: 1.29 ms against 1.40 for the LDS bucket kernel this
+// replaces (1.27 without the comparison of neighbours that flags a changed
+// pattern, of which 0.92 with synthetic columns, 0.90 without the stores, 1.22
+// without the sort; 414 vector instructions a row against 582).  Rows that
 // cluster in bands, which that kernel sorted in LDS: 1.45 against 5.40 ms.
 // Rows of 257..512 and 513..1024 products against the block bucket kernel:
 // R-MAT blocks 0.32 against 0.84 ms and 0.13 against 0.18 ms (FP32), ragged
